@@ -352,9 +352,9 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     // per-row selections whose tile slots all fit one list split by logical
     // block: every split then scans all slots and the rows that chose a block
     // in different slots still share its load
-    // entries one split's list holds (per-row selections with an fp8 cache:
+    // entries one split's list holds (per-row selections with an fp8 cache or 64-row tiles:
     // half a list, see the kernel's LDS layout)
-    const int64_t list_cap = per_row && fp8 ? mla::kPerRowListFp8 : mla::kMaxSlotsPerSplit;
+    const int64_t list_cap = per_row && (fp8 || row_groups == 1) ? mla::kPerRowListShort : mla::kMaxSlotsPerSplit;
     const bool by_id = per_row && tile_qrows > 1 && K * tile_qrows <= list_cap;
     int64_t S;
     if (opts && opts->n_splits > 0) {

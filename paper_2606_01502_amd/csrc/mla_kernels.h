@@ -132,7 +132,9 @@ constexpr int kKvFp8Split = 2;   // e4m3, separate ckv and kpe scales per block
 // its stage area, NB * (query rows of the tile) 16-bit counters.
 constexpr int kPerRowCounterBytes = 2 * 64 * 1152 - 64;  // the stage area, less the wave counters
 constexpr int kPerRowMaxRows = 64;                  // query rows per row tile (mask bits)
-constexpr int kPerRowListFp8 = kMaxSlotsPerSplit / 2;  // list entries per split, fp8 caches
+// list entries per split of per-row selections with fp8 caches or 64-row tiles
+// (elsewhere kMaxSlotsPerSplit)
+constexpr int kPerRowListShort = kMaxSlotsPerSplit / 2;
 
 // Selection kinds: one block selection per job, one per query row, or one
 // token selection per job (bf16 caches only for the last two).

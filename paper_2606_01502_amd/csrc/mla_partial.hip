@@ -1,34 +1,37 @@
 // Sparse absorbed-MLA partial attention for gfx950 (MI355X).
 //
-// One workgroup of 4 waves handles one (job, row tile, slot range).  The rows
-// of a job (Mq x H query rows; a row is a 512-wide latent part plus a 64-wide
+// One workgroup handles one (job, row tile, slot range).  The rows of a job
+// (Mq x H query rows; a row is a 512-wide latent part plus a 64-wide
 // decoupled-RoPE part, the paper's d_qk = 576 wire row of Section 3.2) share
 // one selection of 64-token cache blocks, so each selected block is read from
-// HBM once per workgroup and staged in LDS for all of its rows:
+// HBM once per workgroup and staged in LDS for all of its rows.  Two kernels:
+// tiles of 128 rows (partial_kernel, 4 waves) read a block once for twice the
+// rows, tiles of 64 rows (tile64_kernel, 8 waves) finish sooner where few
+// blocks make up a work item; the planner chooses (mla_api.hip).  Both:
 //
 //   gather   direct-to-LDS 16-byte loads (global_load_lds_dwordx4) of each
-//            selected block into LDS, one block (bf16, 72 KiB) or three (fp8
-//            e4m3 codes, 36 KiB) ahead of the block being computed.  The
+//            selected block into LDS, ahead of the block being computed.  The
 //            chunk's block table maps the selected logical block to its pool
 //            block.  Blocks land swizzled, in the layout the reads below use.
-//   S^T      = K . Q^T per wave for its 16*RG rows: bf16 MFMA 16x16x32, K read
-//            from LDS (16-byte reads of bf16, or 8-byte reads of e4m3 codes
-//            converted to bf16 in registers, exactly, between the products),
-//            Q held in registers for the whole kernel.
-//   softmax  online, in the exp2 domain, with wavefront reductions; the
-//            running max only moves when a block raises it by more than 2^8,
-//            so the accumulator is rarely rescaled (exact either way).
-//   O^T     += V^T . P^T per wave for its rows and all 512 latent columns:
-//            bf16 MFMA with P^T taken straight from the S^T accumulator layout
-//            (the k index of the product is a fixed permutation of the block's
-//            tokens) and V^T read with the transposing LDS read
-//            (ds_read_b64_tr_b16, or ds_read_b64_tr_b8 and a conversion in
-//            registers for fp8) from the same stage, since the value is the
-//            latent part of the key (Section 3.2).  O lives in the
-//            accumulation registers for the whole kernel.
+//   S^T      = K . Q^T: bf16 MFMA 16x16x32, K read from LDS (bf16, or e4m3
+//            codes converted to bf16 in registers, exactly, between the
+//            products), Q held in registers for the whole kernel.
+//   softmax  online, in the exp2 domain; the running max only moves when a
+//            block raises it by more than 2^8, so the accumulator is rarely
+//            rescaled (exact either way).
+//   O^T     += V^T . P^T with O in registers for the whole kernel; V^T read with
+//            the transposing LDS reads from the same stage, since the value is
+//            the latent part of the key (Section 3.2).
 //   epilogue normalised output and lse = max + ln(sum) per row, either to the
 //            caller's buffers or, under split-K, to a workspace that the
 //            combine kernel reduces with the merge algebra (Section 3.3).
+//
+// The 128-row kernel gives each wave 32 rows for both contractions: P^T goes
+// straight from the S^T accumulators to the value product (the k index of that
+// product is a fixed permutation of the block's tokens), and every wave reads
+// all keys and values.  The 64-row kernel splits S^T over rows and tokens and
+// O^T over columns, so that each value is read by one wave only, and passes P
+// through LDS; see there.
 //
 // fp8 per-block scales (Section 6.3 mentions an FP8 sparse kernel; the scale
 // granularity is this library's) stay out of the bf16 operands, which hold the
@@ -47,7 +50,7 @@
 // fp16 scaled by the row's largest magnitude.
 //
 // LDS swizzles (token t of the block, 16-byte chunk c of its row) are
-// described with bf16_key and fp8_key below.
+// described with bf16_key, fp8_key and key32 below.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -65,6 +68,8 @@ typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef short i16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef int i32x2_t __attribute__((ext_vector_type(2)));
 typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
 
@@ -82,6 +87,8 @@ typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
 // stage area, which no load writes before the compaction is over.
 template <bool FP8>
 struct Layout {
+  static constexpr bool kFp8 = FP8;
+  static constexpr int kThreads = 256;
   static constexpr int kElt = FP8 ? 1 : 2;                     // bytes per element
   static constexpr int kRow = kDLat * kElt;                    // latent row
   static constexpr int kRopeRow = kDPe * kElt;                 // RoPE row
@@ -103,7 +110,7 @@ struct Layout {
 };
 static_assert(Layout<true>::kMasks + Layout<true>::kPerRowCap * 8 <= Layout<true>::kTotal,
               "fp8 per-row scales and masks fit the scale area");
-static_assert(Layout<true>::kPerRowCap == kPerRowListFp8, "per-row fp8 list size");
+static_assert(Layout<true>::kPerRowCap == kPerRowListShort, "per-row fp8 list size");
 static_assert(Layout<true>::kTotal <= 160 * 1024 && Layout<false>::kTotalPerRow <= 160 * 1024,
               "LDS budget");
 static_assert(kPerRowCounterBytes <= Layout<false>::kWaveCnt && kPerRowCounterBytes <= Layout<true>::kWaveCnt,
@@ -538,17 +545,17 @@ __device__ __forceinline__ void put_fp8_factors(LDS float* scales, int i, float 
 // into the LDS list (slot order kept); for fp8 also each listed block's
 // factors (put_fp8_factors).  first_id: the id of slot slot0 + tid, already
 // loaded (see first_slot_id).  Returns the number of listed blocks.
-template <bool FP8>
+template <class L>
 __device__ __forceinline__ int compact_slots(const PartialParams& p, int r, int slot0, int nslots,
                                              int first_id, LDS uint8_t* smem, int tid) {
-  using L = Layout<FP8>;
+  constexpr bool FP8 = L::kFp8;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   LDS int* list = (LDS int*)(smem + L::kList);
   LDS float* scales = (LDS float*)(smem + L::kScales);
   LDS int* wave_cnt = (LDS int*)(smem + L::kWaveCnt);
   int n_valid = 0;
-  for (int base = 0; base < nslots; base += 256) {
+  for (int base = 0; base < nslots; base += L::kThreads) {
     const int i = base + tid;
     int b = -1;
     if (i < nslots) {
@@ -564,7 +571,7 @@ __device__ __forceinline__ int compact_slots(const PartialParams& p, int r, int 
     lds_barrier();
     int off = n_valid, total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < L::kThreads / 64; ++w) {
       const int c = wave_cnt[w];
       off += (w < wave) ? c : 0;
       total += c;
@@ -592,23 +599,24 @@ __device__ __forceinline__ int compact_slots(const PartialParams& p, int r, int 
 // fp8: each entry also gets its block's factors (put_fp8_factors).
 // first_id: the id of this thread's first entry (row i0 + tid / nslots, slot
 // slot0 + tid % nslots), already loaded.
-template <bool FP8>
+template <class L>
 __device__ __forceinline__ int compact_per_row(const PartialParams& p, int r, int slot0,
                                                int nslots, int id0, int id_step, int i0, int n_i,
                                                int first_id, LDS uint8_t* smem, LDS int* list,
                                                LDS uint64_t* masks, int tid) {
+  constexpr bool FP8 = L::kFp8;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   LDS uint32_t* cnt = (LDS uint32_t*)smem;
   LDS const uint16_t* cnt16 = (LDS const uint16_t*)smem;
-  LDS int* wave_cnt = (LDS int*)(smem + Layout<FP8>::kWaveCnt);
-  LDS float* scales = (LDS float*)(smem + Layout<FP8>::kScales);
+  LDS int* wave_cnt = (LDS int*)(smem + L::kWaveCnt);
+  LDS float* scales = (LDS float*)(smem + L::kScales);
   const int n_ids = id0 < p.NB ? (p.NB - id0 + id_step - 1) / id_step : 0;
   const int n_words = (n_ids * n_i + 1) >> 1;
-  for (int w = tid; w < n_words; w += 256) cnt[w] = 0u;
+  for (int w = tid; w < n_words; w += L::kThreads) cnt[w] = 0u;
   lds_barrier();
   const int n_ent = n_i * nslots;
-  for (int e = tid; e < n_ent; e += 256) {
+  for (int e = tid; e < n_ent; e += L::kThreads) {
     const int ii = e / nslots, j = e - ii * nslots;
     const int id = e == tid ? first_id : p.sel[r * p.sel_s0 + (int64_t)(i0 + ii) * p.sel_s1 + slot0 + j];
     const int u = (id - id0) / id_step;
@@ -622,7 +630,7 @@ __device__ __forceinline__ int compact_per_row(const PartialParams& p, int r, in
   }
   lds_barrier();
   int n_valid = 0;
-  for (int base = 0; base < n_ids; base += 256) {
+  for (int base = 0; base < n_ids; base += L::kThreads) {
     const int u = base + tid, id = id0 + u * id_step;
     int kmax = 0;
     if (u < n_ids)
@@ -638,7 +646,7 @@ __device__ __forceinline__ int compact_per_row(const PartialParams& p, int r, in
     lds_barrier();
     int off = n_valid + incl - kmax, total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < L::kThreads / 64; ++w) {
       const int c = wave_cnt[w];
       off += (w < wave) ? c : 0;
       total += c;
@@ -675,11 +683,11 @@ __device__ __forceinline__ int compact_per_row(const PartialParams& p, int r, in
 // the RoPE ratio in tok_scales[kMaxSlotsPerSplit + i] and the score factor
 // in tok_scales[2 kMaxSlotsPerSplit + i].  Returns the number of listed
 // tokens.
-template <bool FP8>
+template <class L>
 __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int slot0,
                                               int nslots, int first_id, LDS uint8_t* smem,
                                               int tid) {
-  using L = Layout<FP8>;
+  constexpr bool FP8 = L::kFp8;
   LDS float* tok_scales = (LDS float*)(smem + L::kScales);
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -687,7 +695,7 @@ __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int
   LDS int* wave_cnt = (LDS int*)(smem + L::kWaveCnt);
   const int64_t n_ids = (int64_t)p.NB * kBlock;
   int n_tok = 0;
-  for (int base = 0; base < nslots; base += 256) {
+  for (int base = 0; base < nslots; base += L::kThreads) {
     const int i = base + tid;
     int pt = -1;
     if (i < nslots) {
@@ -703,7 +711,7 @@ __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int
     lds_barrier();
     int off = n_tok, total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < L::kThreads / 64; ++w) {
       const int c = wave_cnt[w];
       off += (w < wave) ? c : 0;
       total += c;
@@ -724,7 +732,7 @@ __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int
     lds_barrier();
   }
   const int padded = (n_tok + kBlock - 1) & ~(kBlock - 1);
-  for (int i = tid; i < padded; i += 256) {
+  for (int i = tid; i < padded; i += L::kThreads) {
     if (i >= n_tok) {
       list[i] = list[0];
       if constexpr (FP8) {
@@ -738,13 +746,16 @@ __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int
   return n_tok;
 }
 
-// RG row groups of 16 per wave: wave w computes rows 16*RG*w .. 16*RG*(w+1)-1
-// of the row tile (64*RG rows) over all 512 latent columns.  KV is the cache
+// ---- the 128-row kernel.
+//
+// RG = 2 row groups of 16 per wave: wave w computes rows 32w .. 32w+31 of the
+// row tile over all 512 latent columns.  KV is the cache
 // kind: bf16, e4m3 with one scale per block for the whole 576-wide entries, or
 // e4m3 with separate latent and RoPE scales per block.
-template <int RG, int KV, int SEL>
+template <int KV, int SEL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void partial_kernel(const PartialParams p) {
+  constexpr int RG = 2;
   constexpr bool FP8 = KV != kKvBf16;
   constexpr bool PR = SEL == kSelPerRow;   // a block selection per query row
   constexpr bool TOK = SEL == kSelTokens;  // token selections, 64 to a virtual block
@@ -837,14 +848,14 @@ void partial_kernel(const PartialParams p) {
   int n_valid;
   int n_tok = 0;  // token selections: the listed tokens (n_valid counts virtual blocks)
   if constexpr (PR) {
-    n_valid = compact_per_row<FP8>(p, r, c_slot0, c_nslots, p.split_by_id ? s_idx : 0,
+    n_valid = compact_per_row<L>(p, r, c_slot0, c_nslots, p.split_by_id ? s_idx : 0,
                                    p.split_by_id ? p.n_splits : 1, i0, n_i, first_id, smem, list,
                                    masks, tid);
   } else if constexpr (TOK) {
-    n_tok = compact_tokens<FP8>(p, r, slot0, nslots, first_id, smem, tid);
+    n_tok = compact_tokens<L>(p, r, slot0, nslots, first_id, smem, tid);
     n_valid = (n_tok + kBlock - 1) / kBlock;
   } else {
-    n_valid = compact_slots<FP8>(p, r, slot0, nslots, first_id, smem, tid);
+    n_valid = compact_slots<L>(p, r, slot0, nslots, first_id, smem, tid);
   }
 
   // the first blocks' loads
@@ -1373,14 +1384,879 @@ void partial_kernel(const PartialParams p) {
   }
 }
 
+// ---- the 64-row kernel.
+//
+// What bounds a short work item (a split of a few blocks) is the chain of
+// latencies around its blocks and, in the block itself, the instructions one
+// wave can issue: a wave issues one instruction per about 5 clocks, whatever
+// kind, so with one wave on a SIMD 16 clocks of product leave room for two
+// others.  Eight waves, two on a SIMD, share a tile:
+//   S^T   wave w: rows 16 (w & 3) .. +15 x tokens 16 (w >> 2) .. +15 of a stage
+//         of 32 tokens.  Each key is read by four waves.
+//   O^T   wave w: all 64 rows x columns 64 w .. +63, with 32x32x16 products.
+//         Each value is read by one wave; the transposing reads run at half the
+//         rate of plain ones (128 bytes a clock and CU, measured), so that four
+//         waves reading all values took as long as all products.
+//   P     through LDS, 4 KiB a stage.
+// In a pipeline over 32-token stages: while the value products of stage i run,
+// the softmax of stage i + 1 is computed between them, with one barrier a
+// stage.  Measured against 4 waves of 16 rows, each with all keys and values
+// (partial call, us): one request x 128 heads x 32 blocks 17.2 -> 14.6, 16
+// requests x 64 rows x 32 blocks 23.5 -> 20.7, 256 requesters x 16 heads on 32
+// blocks 35.8 -> 30.4, 64 of them with 32 of 128 blocks each 34.7 -> 29.5, fp8
+// with 120 rows x 47 blocks 28.1 -> 24.1, 16 rows x 2 blocks 9.8 -> 9.3.  Four
+// waves with this split of the work: 16.2, 21.7, 31.9, 32.7, 24.9 and 11.1.
+//
+// LDS of a 64-row tile: a ring of 32-token stages (half a block: bf16 four of
+// 36 KiB, fp8 six of 18 KiB of codes), the block list with its fp8 factors and
+// row masks, two buffers of weights P (4 KiB each) and the waves' exchange
+// area.  The query rows pass through the stages after the first two before any
+// tokens do (72 KiB).
+template <bool FP8, bool PR>
+struct Tile {
+  static constexpr bool kFp8 = FP8;
+  static constexpr int kThreads = 512;
+  static constexpr int kElt = FP8 ? 1 : 2;
+  static constexpr int kRow = kDLat * kElt;                  // latent row
+  static constexpr int kRopeRow = kDPe * kElt;               // RoPE row
+  static constexpr int kTok = 32;                            // tokens of a stage
+  static constexpr int kStageCkv = kTok * kRow;
+  static constexpr int kStage = kStageCkv + kTok * kRopeRow;
+  static constexpr int kNum = FP8 ? 6 : 4;
+  static constexpr int kLoads = FP8 ? 3 : 5;  // direct-to-LDS loads per wave per stage
+  static constexpr int kQ = 2 * kStage;       // the query rows' place: 64 rows of 1 KiB, then of 128 B
+  static constexpr int kCap = PR ? kPerRowListShort : kMaxSlotsPerSplit;
+  // per-row selections: the compaction's counters take up to kPerRowCounterBytes
+  // from the start; what it writes lies past them (fp8: the rest in between)
+  static constexpr int kRing = kNum * kStage;
+  static constexpr int kList = PR ? (kPerRowCounterBytes + 255) / 256 * 256 : kRing;
+  static constexpr int kScales = kList + kCap * 4;
+  static constexpr int kMasks = kScales + (FP8 ? kCap * 12 : 0);
+  static constexpr int kWaveCnt = kMasks + (PR ? kCap * 8 : 0);
+  static constexpr int kP = FP8 && PR ? kRing : kWaveCnt + 256;
+  static constexpr int kX = kP + 8192;       // row maxima [64 rows][2 token groups]
+  static constexpr int kFlags = kX + 512;    // a byte per wave and lane
+  static constexpr int kTotal = FP8 && PR ? kWaveCnt + 32 : kFlags + 512;
+  static_assert(kRing <= kList && kFlags + 512 <= (FP8 && PR ? kList : kTotal), "areas apart");
+};
+static_assert(Tile<false, true>::kTotal <= 160 * 1024 && Tile<true, true>::kTotal <= 160 * 1024 &&
+                  Tile<true, false>::kTotal <= 160 * 1024 && Tile<false, false>::kTotal <= 160 * 1024,
+              "LDS budget");
+static_assert(Tile<true, false>::kQ + 65536 + 8192 <= Tile<true, false>::kRing &&
+                  Tile<false, false>::kQ + 65536 + 8192 <= Tile<false, false>::kRing,
+              "the query rows fit the stages after the first");
+
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+// One S^T product of 16 tokens x 16 rows x 32 dims (see st1: kPad ends with 24
+// wait states, after which VALU code may read c; kPre leads with 3, for an
+// operand just written).
+template <bool kFirst, bool kPad, bool kPre>
+__device__ __forceinline__ void stq(f32x4_t& c, bf16x8_t a, bf16x8_t q) {
+  if constexpr (kFirst && kPre)
+    asm volatile("s_nop 2\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(q));
+  else if constexpr (kFirst)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(q));
+  else if constexpr (kPad)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7"
+                 : "+v"(c) : "v"(a), "v"(q));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(q));
+}
+
+// One O^T product of 32 columns x 32 rows x 16 tokens, in place: left to the
+// compiler, the accumulators get two sets of registers where paths meet.
+template <bool kPre>  // leads with 3 wait states, for an operand just written
+__device__ __forceinline__ void pv(f32x16_t& c, bf16x8_t v, bf16x8_t w) {
+  if constexpr (kPre)
+    asm volatile("s_nop 2\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(v), "v"(w));
+  else
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(v), "v"(w));
+}
+
+// O[d][k] *= alpha[k] when `any` (wave-uniform) is set.  One asm statement,
+// branch included, over fixed registers: as a conditional block the scaled
+// values would be new ones to the compiler, and it copies all of O where the
+// paths meet, in every step.
+#define MLA_MUL4(a, b, c, d, by)                                                       \
+  "v_mul_f32 v" #a ", v" #a ", " by "\n\tv_mul_f32 v" #b ", v" #b ", " by "\n\t"       \
+  "v_mul_f32 v" #c ", v" #c ", " by "\n\tv_mul_f32 v" #d ", v" #d ", " by "\n\t"
+__device__ __forceinline__ void scale_all(f32x16_t (&O)[2][2], const float (&alpha)[2], int any) {
+  asm volatile("s_cmp_eq_u32 %6, 0\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+      MLA_MUL4(0, 1, 2, 3, "%4") MLA_MUL4(4, 5, 6, 7, "%4")
+      MLA_MUL4(8, 9, 10, 11, "%4") MLA_MUL4(12, 13, 14, 15, "%4")
+      MLA_MUL4(16, 17, 18, 19, "%5") MLA_MUL4(20, 21, 22, 23, "%5")
+      MLA_MUL4(24, 25, 26, 27, "%5") MLA_MUL4(28, 29, 30, 31, "%5")
+      MLA_MUL4(32, 33, 34, 35, "%4") MLA_MUL4(36, 37, 38, 39, "%4")
+      MLA_MUL4(40, 41, 42, 43, "%4") MLA_MUL4(44, 45, 46, 47, "%4")
+      MLA_MUL4(48, 49, 50, 51, "%5") MLA_MUL4(52, 53, 54, 55, "%5")
+      MLA_MUL4(56, 57, 58, 59, "%5") MLA_MUL4(60, 61, 62, 63, "%5")
+      "s_nop 2\n.Lkeep%=:"
+      : "+{v[0:15]}"(O[0][0]), "+{v[16:31]}"(O[0][1]), "+{v[32:47]}"(O[1][0]), "+{v[48:63]}"(O[1][1])
+      : "v"(alpha[0]), "v"(alpha[1]), "s"(__builtin_amdgcn_readfirstlane(any))
+      : "scc");
+}
+#undef MLA_MUL4
+
+// A pointer that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ __forceinline__ const T* uniform(const T* a) {
+  const uint64_t u = (uint64_t)(uintptr_t)a;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (const T*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+
+// The larger of lanes l and l ^ 32.
+__device__ __forceinline__ float xor32_max(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+// Swizzles of a 64-row tile's stages (16-byte chunk c of latent row t in slot
+// c ^ key32(t), of RoPE row t in slot c ^ rope_key32(t)).  A key read takes
+// chunk 4 i + g of token 16 th + n for lane (n, g); the LDS serves 16 lanes of
+// a 16-byte read at once, those of the 4-lane groups of one parity, i.e. n in
+// {0..3, 8..11} (or the others) with two neighbouring g: the key puts n & 3
+// and n >> 3 where the chunk's own bits are not.  A transposing value read
+// serves 16 lanes too: 4 tokens x 2 neighbouring chunks (bf16), 8 tokens (0..3
+// and 8..11, say) x 1 chunk (fp8).  All are conflict free.
+__device__ __forceinline__ int key32(int t) {
+  return ((t & 3) << 2) | (((t >> 3) & 1) << 1) | ((t >> 4) & 1);
+}
+template <bool FP8>
+__device__ __forceinline__ int rope_key32(int t) {
+  return FP8 ? ((t >> 3) & 1) << 1 : (((t >> 1) & 1) << 1) | (((t >> 3) & 1) << 2);
+}
+
+// The direct-to-LDS loads of a stage: 32 tokens, half h & 1 of listed block
+// h >> 1 (or 32 listed tokens).
+//   bf16: load j < 4 of wave w is latent row 4w + j (lane -> slot lane); load 4
+//         is RoPE rows 4w + (lane >> 3), slot lane & 7, by 32 lanes.
+//   fp8:  load j < 2 of wave w is latent rows 4w + 2j + (lane >> 5), slot
+//         lane & 31; load 2 is RoPE rows 4w + (lane >> 2), slot lane & 3, by 16
+//         lanes.
+// The latent loads of a wave share M0 and the scalar base: the instruction's
+// offset moves both the source and the place in LDS.  The lane's offset
+// differs between them by an XOR (the key of the row's low bits), held for each.
+template <bool FP8, bool TOK>
+struct Issue32 {
+  using L = Tile<FP8, false>;
+  static constexpr int kLat = L::kLoads - 1;
+  uint32_t lat[kLat], rope;
+  const uint8_t* ckv;  // the wave's first row
+  const uint8_t* kpe;
+  uint32_t lds_lat, lds_rope;  // LDS addresses of the wave's first rows
+  int tok, tok_rope;  // TOK: pool tokens of stage tokens 4w + (lane & 3) and of the RoPE load's row
+
+  __device__ __forceinline__ Issue32(const PartialParams& p, int wave, int lane) {
+    ckv = p.ckv;
+    kpe = p.kpe;
+    lds_lat = lds_rope = 0;
+    tok = tok_rope = 0;
+    const int b3 = (wave >> 1) & 1;           // bit 3 of the wave's rows
+    const int kw = (b3 << 1) | (wave >> 2);   // their key32, less the low bits' part
+    const int hi = lane >> 5;
+#pragma unroll
+    for (int k = 0; k < kLat; ++k)
+      lat[k] = FP8 ? (uint32_t)(hi * 512 + (((lane & 31) ^ (hi << 2) ^ kw ^ (k << 3)) << 4))
+                   : (uint32_t)((lane ^ kw ^ (k << 2)) << 4);
+    rope = FP8 ? (uint32_t)((lane >> 2) * 64 + (((lane & 3) ^ (b3 << 1)) << 4))
+               : (uint32_t)((lane >> 3) * 128 + (((lane & 7) ^ ((((lane >> 4) & 1) << 1) | (b3 << 2))) << 4));
+  }
+  // what aim() needs of the list for half block h, read ahead of it
+  __device__ __forceinline__ void look(const LDS int* list, int h, int wave, int lane, int (&e)[2]) const {
+    if constexpr (TOK) {
+      e[0] = list[h * 32 + 4 * wave + (lane & 3)];
+      e[1] = list[h * 32 + 4 * wave + ((FP8 ? lane >> 2 : lane >> 3) & 3)];
+    } else {
+      e[0] = list[h >> 1];
+    }
+  }
+  // points the loads at half block h and stage buf
+  __device__ __forceinline__ void aim(const PartialParams& p, const int (&e)[2], int h, uint32_t buf, int wave) {
+    if constexpr (TOK) {
+      tok = e[0];
+      tok_rope = e[1];
+    } else {
+      const int64_t b = (int64_t)__builtin_amdgcn_readfirstlane(e[0]) * 2 + (h & 1);
+      ckv = p.ckv + b * L::kStageCkv + wave * (4 * L::kRow);
+      kpe = p.kpe + b * (32 * L::kRopeRow) + wave * (4 * L::kRopeRow);
+    }
+    lds_lat = __builtin_amdgcn_readfirstlane(buf + (uint32_t)wave * (4 * L::kRow));
+    lds_rope = __builtin_amdgcn_readfirstlane(buf + (uint32_t)L::kStageCkv + (uint32_t)wave * (4 * L::kRopeRow));
+  }
+  __device__ __forceinline__ static void go(uint32_t off, const uint8_t* base, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(off), "s"(uniform(base)), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+  }
+  __device__ __forceinline__ static void go64(const uint8_t* a, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(a), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+  }
+  // Load j; every lane of the wave is active where this is called.
+  __device__ __forceinline__ void load(const PartialParams& p, int j, int lane) const {
+    if (j < kLat) {
+      if constexpr (!TOK) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                     :: "v"(lat[j]), "s"(uniform(ckv)), "s"(__builtin_amdgcn_readfirstlane(lds_lat)), "i"(j * 1024)
+                     : "memory", "m0");
+      } else if constexpr (FP8) {
+        const uint32_t t = (uint32_t)__shfl(tok, 2 * j + (lane >> 5));
+        go64(p.ckv + (uint64_t)t * 512u + (lat[j] & 0x1f0u), lds_lat + (uint32_t)j * 1024u);
+      } else {
+        const uint32_t t = (uint32_t)__builtin_amdgcn_readlane(tok, j);
+        go(lat[j], p.ckv + (uint64_t)t * 1024u, lds_lat + (uint32_t)j * 1024u);
+      }
+    } else {
+      // the first 32 (fp8: 16) lanes only
+      constexpr uint64_t kLanes = FP8 ? 0xffffull : 0xffffffffull;
+      if constexpr (!TOK) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                     :: "v"(rope), "s"(uniform(kpe)), "s"(__builtin_amdgcn_readfirstlane(lds_rope)), "s"(kLanes)
+                     : "memory", "m0");
+      } else {
+        const uint8_t* a = p.kpe + (uint64_t)(uint32_t)tok_rope * L::kRopeRow + (rope & (FP8 ? 0x30u : 0x70u));
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
+                     :: "v"(a), "s"(__builtin_amdgcn_readfirstlane(lds_rope)), "s"(kLanes) : "memory", "m0");
+      }
+    }
+  }
+};
+
+template <int KV, int SEL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tile64_kernel(const PartialParams p) {
+  constexpr bool FP8 = KV != kKvBf16;
+  constexpr bool PR = SEL == kSelPerRow;
+  constexpr bool TOK = SEL == kSelTokens;
+  constexpr bool kSplitScales = KV == kKvFp8Split;
+  using L = Tile<FP8, PR>;
+  __shared__ __attribute__((aligned(16))) uint8_t smem_raw[L::kTotal];
+  LDS uint8_t* smem = (LDS uint8_t*)smem_raw;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rq = wave & 3;   // S^T: rows 16 rq .. 16 rq + 15 of the tile
+  const int th = wave >> 2;  // S^T: tokens 16 th .. 16 th + 15 of a stage
+  const int n16 = lane & 15, g = lane >> 4;  // S^T: row (or token) and dim group
+  const int n32 = lane & 31, g2 = lane >> 5;  // O^T: row (or column) and token group
+
+  const int w_id = gridDim.x % 8 ? (int)blockIdx.x
+                                 : (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+  const bool tiles_fast = PR && p.tiles_fast;
+  const int s_idx = tiles_fast ? (w_id / p.row_tiles) % p.n_splits : w_id % p.n_splits;
+  const int rt = tiles_fast ? w_id % p.row_tiles : (w_id / p.n_splits) % p.row_tiles;
+  const int r_num = w_id / (p.n_splits * p.row_tiles);
+  const int r = p.q_rep > 1 ? (r_num % p.q_rep) * p.q_jobs + r_num / p.q_rep : r_num;
+  const int qj = r % p.q_jobs;  // the job's query rows
+  const int slot0 = s_idx * p.slots_per_split;
+  const int nslots = max(0, min(p.K - slot0, p.slots_per_split));
+
+  LDS int* list = (LDS int*)(smem + L::kList);
+  LDS float* scales = (LDS float*)(smem + L::kScales);
+  LDS uint64_t* masks = (LDS uint64_t*)(smem + L::kMasks);
+  LDS uint8_t* const pbuf = smem + L::kP;
+  LDS float* const xmax = (LDS float*)(smem + L::kX);
+  LDS uint8_t* const flags = smem + L::kFlags;
+  const int row_wg0 = rt * 64;
+  const int i0 = row_wg0 / p.H;
+  const int n_i = PR ? (min(row_wg0 + 64, p.rows) - 1) / p.H - i0 + 1 : 1;
+  const int c_slot0 = PR && p.split_by_id ? 0 : slot0;
+  const int c_nslots = PR && p.split_by_id ? p.K : nslots;
+  int first_id = -1;
+  if constexpr (PR) {
+    if (tid < n_i * c_nslots) {
+      const int ii = tid / c_nslots, j = tid - ii * c_nslots;
+      first_id = p.sel[r * p.sel_s0 + (int64_t)(i0 + ii) * p.sel_s1 + c_slot0 + j];
+    }
+  } else {
+    if (tid < nslots) first_id = p.sel[r * p.sel_s0 + slot0 + tid];
+  }
+
+  // query rows to LDS: wave w loads rows 8w .. 8w+7 of the tile (rows past the
+  // job's end repeat its last row; they are never stored)
+  auto issue_q = [&]() {
+    const int row0 = row_wg0 + 8 * wave;
+    const int rc = min(row0, p.rows - 1);
+    const int qi = __builtin_amdgcn_readfirstlane(rc / p.H);
+    int qh = rc - qi * p.H;
+    const uint16_t* ql = p.q_lat + (qj * p.ql_s0 + qi * p.ql_s1 + qh * p.ql_s2);
+    const int64_t wrap = p.ql_s1 - (int64_t)(p.H - 1) * p.ql_s2;
+    // key32 of rows 8 w + j, less j's part
+    const uint32_t lat = (uint32_t)((lane ^ (((wave & 1) << 1) | ((wave >> 1) & 1))) << 4);
+    const uint32_t dst = lds0 + L::kQ + wave * 8192;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      Issue32<false, false>::go(lat ^ (uint32_t)((j & 3) << 6), (const uint8_t*)ql, dst + (uint32_t)j * 1024u);
+      if (row0 + j + 1 < p.rows) {
+        const bool w = qh + 1 == p.H;
+        ql += w ? wrap : p.ql_s2;
+        qh = w ? 0 : qh + 1;
+      }
+    }
+    const int t = 8 * wave + (lane >> 3);
+    const int row = min(row_wg0 + t, p.rows - 1);
+    const int i = row / p.H, h = row - i * p.H;
+    const int c = (lane & 7) ^ rope_key32<false>(t);
+    const uint16_t* src = p.q_pe + (qj * p.qp_s0 + i * p.qp_s1 + h * p.qp_s2) + 8 * c;
+    Issue32<false, false>::go64((const uint8_t*)src, lds0 + L::kQ + 65536 + wave * 1024);
+  };
+  // (the per-row compaction's counters may reach into the query rows' place)
+  bool q_early = true;
+  if constexpr (PR) {
+    const int step = p.split_by_id ? p.n_splits : 1;
+    q_early = (int64_t)((p.NB + step - 1) / step) * n_i * 2 + 4 <= L::kQ;
+  }
+  if (q_early) issue_q();
+
+  int n_valid;
+  int n_tok = 0;
+  if constexpr (PR) {
+    n_valid = compact_per_row<L>(p, r, c_slot0, c_nslots, p.split_by_id ? s_idx : 0,
+                                 p.split_by_id ? p.n_splits : 1, i0, n_i, first_id, smem, list,
+                                 masks, tid);
+  } else if constexpr (TOK) {
+    n_tok = compact_tokens<L>(p, r, slot0, nslots, first_id, smem, tid);
+    n_valid = (n_tok + kBlock - 1) / kBlock;
+  } else {
+    n_valid = compact_slots<L>(p, r, slot0, nslots, first_id, smem, tid);
+  }
+  if (!q_early) issue_q();
+  const int n = TOK ? (n_tok + 31) / 32 : 2 * n_valid;  // stages of tokens
+
+  Issue32<FP8, TOK> is(p, wave, lane);
+  int ahead[2] = {0, 0};  // the list entry of the stage to load next
+  auto aim = [&](int h) { is.aim(p, ahead, h, lds0 + (uint32_t)((h % L::kNum) * L::kStage), wave); };
+  auto issue = [&](int h) {
+    if (h >= n) return;
+    is.look(list, h, wave, lane, ahead);
+    aim(h);
+#pragma unroll
+    for (int j = 0; j < L::kLoads; ++j) is.load(p, j, lane);
+  };
+  issue(0);
+  issue(1);
+  // the query rows have landed
+  if (n > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * L::kLoads));
+  else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  lds_barrier();
+  // This wave's query rows as MFMA B operands, held for the whole kernel: steps
+  // 0, 1 RoPE, 2 .. 17 latent, 32 dims each.  bf16: lane group g takes the
+  // step's dims 8 g .. +7.  fp8: two steps share the 16-byte key reads of 64
+  // dims, lane group g dims 16 g .. +15 of them, the even step the first eight
+  // of these and the odd step the others.
+  bf16x8_t qb[18];
+  {
+    const int t = 16 * rq + n16;
+    const LDS uint8_t* const qr = smem + L::kQ + t * 1024;
+    const LDS uint8_t* const qp = smem + L::kQ + 65536 + t * 128;
+    auto chunk = [&](int ks) { return FP8 ? 8 * (ks >> 1) + 2 * g + (ks & 1) : 4 * ks + g; };
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) qb[ks] = lds_b128(qp + ((chunk(ks) ^ rope_key32<false>(t)) << 4));
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) qb[2 + ks] = lds_b128(qr + ((chunk(ks) ^ key32(t)) << 4));
+  }
+  if constexpr (L::kNum > 4) {
+    lds_barrier();  // every wave holds its query rows: their place takes tokens
+#pragma unroll
+    for (int h = 2; h < L::kNum - 2; ++h) issue(h);
+  }
+
+  // O^T: column tile d (columns 64 wave + 32 d ..) x row half
+  f32x16_t O[2][2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) O[d][k] = f32x16_t{};
+  // of row 16 rq + n16: the running maximum, the sum and largest score over this
+  // lane's tokens; m_all: the maxima of rows n32 and 32 + n32
+  float m_run = -INFINITY, l_run = 0.f, m_true = -INFINITY;
+  float m_all[2] = {-INFINITY, -INFINITY};
+  const int row_bit = PR ? min(max((row_wg0 + 16 * rq + n16) / p.H - i0, 0), 63) : 0;
+
+  // loop-invariant LDS addresses, less the stage
+  constexpr int kRopeReads = FP8 ? 1 : 2, kReads = FP8 ? 9 : 18;
+  uint32_t k_off[4], r_off[kRopeReads], v_off[4], p_put;
+  {
+    const int t = 16 * th + n16;
+    // chunk 4 i + g sits in slot (4 i + g) ^ key: one address for each i & 3,
+    // the rest is an immediate offset
+#pragma unroll
+    for (int i = 0; i < 4; ++i) k_off[i] = lds0 + (uint32_t)(t * L::kRow + (((4 * i + g) ^ key32(t)) << 4));
+#pragma unroll
+    for (int i = 0; i < kRopeReads; ++i)
+      r_off[i] = lds0 + (uint32_t)(L::kStageCkv + t * L::kRopeRow + (((4 * i + g) ^ rope_key32<FP8>(t)) << 4));
+    // the value fragment of column tile d and 16 tokens kk.  bf16: two
+    // transposing reads of 4 tokens x 16 columns per 16 lanes (lane i of group
+    // q: tokens 8 (q >> 1) + (i >> 2) and 4 on, columns 16 (q & 1) + 4 (i & 3));
+    // fp8: one of 8 tokens x 16 columns (lane i: token row i >> 1 of tokens
+    // 4 (q >> 1) .. +3 and 8 on, half i & 1).
+    const int q = lane >> 4, i = lane & 15;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const int kk = f >> 1, d = f & 1;
+      if constexpr (FP8) {
+        const int x = (i >> 1) & 3, hh = i >> 3;
+        const int tk = 16 * kk + 8 * hh + 4 * (q >> 1) + x;
+        v_off[f] = lds0 + (uint32_t)(tk * 512 + (((4 * wave + 2 * d + (q & 1)) ^ key32(tk)) << 4) + 8 * (i & 1));
+      } else {
+        const int tk = 16 * kk + 8 * (q >> 1) + (i >> 2);
+        v_off[f] = lds0 + (uint32_t)(tk * 1024 + (((8 * wave + 4 * d + 2 * (q & 1) + ((i >> 1) & 1)) ^ key32(tk)) << 4) + 8 * (i & 1));
+      }
+    }
+    // where the lane's four weights of its row go: fragment (th, row half), in
+    // the order of the value fragments' tokens
+    const int gg = FP8 ? g & 1 : g >> 1, hh = FP8 ? g >> 1 : g & 1;
+    p_put = (uint32_t)(((2 * th + (rq >> 1)) << 10) + ((32 * gg + 16 * (rq & 1) + n16) << 4) + 8 * hh);
+  }
+  auto lds_at = [](uint32_t a) { return (LDS uint8_t*)(uintptr_t)a; };
+
+  // Software pipeline over the stages.  Step i: the last value products of
+  // stage i - 1 (their operands are in registers and cover the latency of the
+  // first key reads), the scores of stage i + 1, then the first value products
+  // of stage i with the softmax of stage i + 1 between them; the loads of
+  // stage i - 1 + kNum go to the ring slot that stage i - 1 left.  One barrier
+  // a step: it publishes stage i + 1, the weights of stage i and the requests
+  // to raise a maximum.
+  f32x4_t sacc, pacc, x;
+  float psum = 0.f;
+  bool on = true;                // of stage x: whether the row attends it
+  float v_mult = 1.f;            // of stage x: the fp8 value scale
+  int x_stage = 0;
+  float s_main = 1.f, s_ratio = 1.f, s_value = 1.f;  // fp8, of the stage whose scores are formed
+  uint64_t s_mask = ~0ull;                            // per-row selections: its row mask
+  LDS const float* const tok_scales = (LDS const float*)(smem + L::kScales);
+  // (element k of a lane's tile is token 16 th + 4 g + k of the stage)
+  auto tok_scale4 = [&](int which, int h) -> f32x4_t {
+    return *(LDS const f32x4_t*)(tok_scales + which * kMaxSlotsPerSplit + h * 32 + 16 * th + 4 * g);
+  };
+  // the weights against the running maximum, their sum, and their bf16 form to LDS
+  auto put_p = [&]() {
+    f32x4_t e;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      e[k] = __builtin_amdgcn_exp2f(x[k] - m_run);
+      if constexpr (PR) e[k] = on ? e[k] : 0.f;
+    }
+    psum = (e[0] + e[1]) + (e[2] + e[3]);
+    if constexpr (FP8 && TOK) e *= tok_scale4(0, x_stage);
+    else if constexpr (FP8) e *= v_mult;
+    *(LDS u16x4_t*)(pbuf + ((x_stage & 1) << 12) + p_put) = f32x4_bf16(e);
+  };
+  // Softmax of a stage over this wave's 16 rows x 16 tokens, in parts.  The
+  // scores, log2 units: the products are rounded before a maximum is taken off
+  // them (opaque to contraction): under a scale of 2^64 a fused
+  // multiply-subtract would leave the rounding error of the maximum itself.
+  float mx = 0.f;
+  auto soft = [&](int part, int stage) {
+    if (part == 0) {
+      x_stage = stage;
+      // (fp8, see fp8_factors: scores are main * (latent part + ratio * RoPE
+      // part); P is scaled by the latent scale before its bf16 rounding)
+      v_mult = s_value;
+      if constexpr (PR) on = ((s_mask >> row_bit) & 1ull) != 0;
+      f32x4_t s = sacc;
+      if constexpr (kSplitScales) {
+        f32x4_t ratio{s_ratio, s_ratio, s_ratio, s_ratio};
+        if constexpr (TOK) ratio = tok_scale4(1, x_stage);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[k] = __builtin_fmaf(pacc[k], ratio[k], s[k]);
+      }
+      if constexpr (FP8 && TOK) x = s * (tok_scale4(2, x_stage) * p.scale_log2);
+      else if constexpr (FP8) x = s * (p.scale_log2 * s_main);
+      else x = s * p.scale_log2;
+      asm("" : "+v"(x));
+      if constexpr (TOK) {
+        const int n_here = n_tok - x_stage * 32 - 16 * th;
+        if (n_here < 16) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (4 * g + k >= n_here) x[k] = -INFINITY;
+        }
+      }
+      mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+      // (a row that does not attend this entry: no maximum, no weights)
+      if (PR && !on) mx = -INFINITY;
+      m_true = fmaxf(m_true, mx);
+    } else if (part == 1) {
+      flags[8 * lane + wave] = mx > m_run + kTau;
+    } else {
+      put_p();
+    }
+  };
+
+  // value fragments: f = 2 kk + d of the stage being added to O; the last one is
+  // left to the next step
+  constexpr int kPvAhead = 3;
+  using VRing = typename std::conditional<FP8, i32x2_t, bf16x8_t>::type;
+  VRing vr[4];
+  bf16x8_t vc[4];     // fp8: the converted fragments
+  bf16x8_t pb[2][2];  // weights [16 tokens][row half]
+  uint32_t v_st = 0;
+  auto vload = [&](int f) {
+    LDS uint8_t* const a = lds_at(v_off[f] + v_st);
+    if constexpr (FP8) {
+      vr[f] = __builtin_bit_cast(i32x2_t, __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS i32x2_t*)a));
+    } else {
+      const i16x4_t lo = lds_tr16(a), hi = lds_tr16(a + 4096);
+      vr[f] = __builtin_bit_cast(bf16x8_t, i16x8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    }
+  };
+  auto vconv = [&](int f) {
+    if constexpr (FP8) {
+      vc[f] = e4m3x8_bf16((uint32_t)vr[f][0], (uint32_t)vr[f][1]);
+      pin(vc[f]);
+    }
+  };
+  auto pload = [&](int i, int kk) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      pb[kk][k] = lds_b128(pbuf + ((i & 1) << 12) + ((2 * kk + k) << 10) + (lane << 4));
+  };
+  auto pv_one = [&](int f, int k, bool pre) {
+    bf16x8_t v;
+    if constexpr (FP8) v = vc[f];
+    else v = vr[f];
+    __builtin_amdgcn_sched_barrier(0);
+    if (pre) pv<true>(O[f & 1][k], v, pb[f >> 1][k]);
+    else pv<false>(O[f & 1][k], v, pb[f >> 1][k]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // waits until stage i + 1's loads of this wave have landed (the next
+  // kNum - 3 stages' may be in flight) and meets the other waves
+  auto meet = [&](int i) {
+    constexpr int kMore = L::kNum - 3;
+    if (kMore >= 3 && n - 2 - i >= 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * L::kLoads));
+    else if (kMore >= 2 && n - 2 - i >= 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * L::kLoads));
+    else if (n - 2 - i >= 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(L::kLoads));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    lds_barrier();
+  };
+  // Step i up to the scores of stage i + 1.  kMid (not the first step): with
+  // the last value products of stage i - 1, and the first reads of stage i's
+  // values and weights
+  constexpr int kAhead = FP8 ? 3 : 6;  // key reads in flight ahead of their products
+  auto scores = [&](int i, auto mid) -> u32x2_t {
+    constexpr bool kMid = decltype(mid)::value;
+    const uint32_t st = (uint32_t)(((i + 1) % L::kNum) * L::kStage);
+    const int ih = i - 1 + L::kNum;  // the stage to load
+    bf16x8_t kr[kAhead + 1];
+    bf16x8_t ka[4];  // fp8: converted ahead of their products
+    auto key_read = [&](int j) {
+      if (j < kRopeReads) kr[j % (kAhead + 1)] = lds_b128(lds_at(r_off[j] + st));
+      else kr[j % (kAhead + 1)] = lds_b128(lds_at(k_off[(j - kRopeReads) & 3] + st) + ((j - kRopeReads) >> 2) * 256);
+    };
+    auto half_of = [&](int j, int e) -> bf16x8_t {  // fp8: codes 8 e .. 8 e + 7 of read j
+      const u32x4_t w = __builtin_bit_cast(u32x4_t, kr[j % (kAhead + 1)]);
+      return e4m3x8_bf16(w[2 * e], w[2 * e + 1]);
+    };
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) key_read(j);
+    u32x2_t ask{};
+    if constexpr (kMid) ask = *(LDS const u32x2_t*)(flags + 8 * lane);
+    const bool ld = ih < n;
+    if constexpr (kMid) pv_one(3, 0, true);
+    if (ld) aim(ih);
+    if constexpr (kMid) pv_one(3, 1, false);
+    if constexpr (FP8) {
+      ka[0] = half_of(0, 0);
+      ka[1] = half_of(0, 1);
+      pin(ka[0]);
+      pin(ka[1]);
+    }
+    auto steps = [&](auto with_loads) {
+      constexpr bool kLd = decltype(with_loads)::value;
+#pragma unroll
+      for (int step = 0; step < 18; ++step) {
+        bf16x8_t a;
+        if constexpr (FP8) a = ka[step & 3];
+        else a = kr[step % (kAhead + 1)];
+        f32x4_t& acc = kSplitScales && step < 2 ? pacc : sacc;
+        __builtin_amdgcn_sched_barrier(0);
+        if (step == 0 || (kSplitScales && step == 2)) stq<true, false, FP8>(acc, a, qb[step]);
+        else if (step == 17) stq<false, true, false>(acc, a, qb[step]);
+        else stq<false, false, false>(acc, a, qb[step]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FP8) {
+          if ((step & 1) == 0 && step / 2 + kAhead < kReads) key_read(step / 2 + kAhead);
+          if (step + 2 < 18) {
+            ka[(step + 2) & 3] = half_of((step + 2) / 2, step & 1);
+            pin(ka[(step + 2) & 3]);
+          }
+        } else {
+          if (step + kAhead < kReads) key_read(step + kAhead);
+        }
+        if (kLd && step % 3 == 1 && step / 3 < L::kLoads) is.load(p, step / 3, lane);
+        // what the softmax and the value products of this step need
+        if (step == 3) {
+          if constexpr (FP8 && !TOK) {
+            const int b = (i + 1) >> 1;
+            s_value = scales[3 * b];
+            s_main = scales[3 * b + 1];
+            if constexpr (kSplitScales) s_ratio = scales[3 * b + 2];
+          }
+          if constexpr (PR) s_mask = masks[(i + 1) >> 1];
+        }
+        if (step == 5) is.look(list, ih + 1, wave, lane, ahead);
+        if constexpr (kMid) {
+          if (step == 12) pload(i, 0);
+          if (step >= 13 && step < 13 + kPvAhead) vload(step - 13);
+        }
+      }
+    };
+    if (ld) steps(std::true_type{});
+    else steps(std::false_type{});
+    return ask;
+  };
+  // Lazy rescale: the maxima move only when some row's grows by more than the
+  // threshold.  Some wave asked for it: every wave takes part, so that all
+  // agree on the new maxima, and the weights of the stage are formed again.
+  // The first stage always comes here, its row maxima exchanged already.
+  auto put_max = [&]() {
+    const float m = xor_max(mx);
+    if (g == 0) xmax[(16 * rq + n16) * 2 + th] = m;
+  };
+  auto settle = [&](int i, u32x2_t ask) {
+    float alpha[2] = {1.f, 1.f};
+    int any = 0;
+    if (i == 0 || __ballot((ask[0] | ask[1]) != 0) != 0) {
+      if (i != 0) {
+        put_max();
+        lds_barrier();
+      }
+      // the new maximum of a row and the factor of what was summed under the old one
+      auto raise = [&](int row, float& m) -> float {
+        const f32x2_t b = *(LDS const f32x2_t*)(xmax + 2 * row);
+        const float bm = fmaxf(b[0], b[1]);
+        float alpha = 1.f;
+        if (bm > m + kTau) {
+          if (m != -INFINITY) alpha = __builtin_amdgcn_exp2f(m - bm);
+          m = bm;
+        }
+        return alpha;
+      };
+      l_run *= raise(16 * rq + n16, m_run);
+      put_p();
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        alpha[k] = raise(32 * k + n32, m_all[k]);
+        any |= __ballot(alpha[k] != 1.f) != 0;
+      }
+      lds_barrier();
+      pload(i, 0);
+    }
+    scale_all(O, alpha, any);
+    l_run += psum;
+  };
+  // O^T[dim][row] += V^T . P^T over this wave's 64 columns and stage i.
+  // kSoft: all but the last fragment, with the softmax of stage i + 1
+  auto values = [&](int i, auto with_soft) {
+    constexpr bool kSoft = decltype(with_soft)::value;
+    if constexpr (FP8) {
+      vconv(0);
+      vconv(1);
+    }
+#pragma unroll
+    for (int f = 0; f < (kSoft ? 3 : 4); ++f) {
+      pv_one(f, 0, FP8 && f == 0);
+      if (f + kPvAhead < 4) vload(f + kPvAhead);
+      if (f == 0) pload(i, 1);
+      if (f + 2 < 4) vconv(f + 2);
+      pv_one(f, 1, false);
+      if (kSoft) soft(f, i + 1);
+    }
+  };
+
+  if (n > 0) {
+    is.look(list, L::kNum - 2, wave, lane, ahead);
+    meet(-1);
+    (void)scores(-1, std::false_type{});
+    soft(0, 0);
+    put_max();
+    // (nothing is left over before the first step: products of zeros)
+    vr[3] = VRing{};
+    vc[3] = bf16x8_t{};
+    pb[1][0] = bf16x8_t{};
+    pb[1][1] = bf16x8_t{};
+    pin(vr[3]);
+    pin(vc[3]);
+    pin(pb[1][0]);
+    pin(pb[1][1]);
+    for (int i = 0; i + 1 < n; ++i) {
+      meet(i);
+      v_st = (uint32_t)((i % L::kNum) * L::kStage);
+      const u32x2_t ask = scores(i, std::true_type{});
+      settle(i, ask);
+      values(i, std::true_type{});
+    }
+    const int i = n - 1;
+    lds_barrier();
+    const u32x2_t ask = *(LDS const u32x2_t*)(flags + 8 * lane);
+    v_st = (uint32_t)((i % L::kNum) * L::kStage);
+    if (n > 1) {
+      pv_one(3, 0, true);
+      pv_one(3, 1, false);
+    }
+    pload(i, 0);
+#pragma unroll
+    for (int f = 0; f < kPvAhead; ++f) vload(f);
+    settle(i, ask);
+    values(i, std::false_type{});
+  }
+
+  // ---- epilogue.  The waves exchange the rows' sums (two token halves),
+  // largest scores and, for fp16 split rows, largest magnitudes (eight column
+  // groups) through the weights' place, then each writes its 64 columns.
+  const bool direct = p.n_splits == 1;
+  const bool half = !direct && p.ws_f16;
+  const int64_t part = (int64_t)r * p.n_splits + s_idx;
+  lds_barrier();  // every wave is done with the last block's weights
+  LDS float* const xsum = (LDS float*)pbuf;       // [64][2]
+  LDS float* const xtrue = xsum + 128;            // [64][2]
+  LDS float* const xamax = xtrue + 128;           // [64][8]
+  {
+    const float l = xor_sum(l_run);
+    const float mt = xor_max(m_true);
+    if (g == 0) {
+      xsum[(16 * rq + n16) * 2 + th] = l;
+      xtrue[(16 * rq + n16) * 2 + th] = mt;
+    }
+  }
+  if (half) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float am = 0.f;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const f32x16_t v = O[d][k];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) am = fmaxf(am, fabsf(v[i]));
+      }
+      am = xor32_max(am);
+      if (g2 == 0) xamax[(32 * k + n32) * 8 + wave] = am;
+    }
+  }
+  lds_barrier();
+  // A lane holds 4 neighbouring columns of row 32 k + n32 at a time, 8 apart;
+  // swaps between lanes l, l ^ 16 (and l, l ^ 32 for 16-bit rows) give each
+  // store instruction 64-byte runs of 16 rows: row 16 j + (lane & 15) of half k.
+  const int q = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int rl = 32 * k + n32;
+    const f32x2_t ls = *(LDS const f32x2_t*)(xsum + 2 * rl);
+    const float l_tot = ls[0] + ls[1];
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    float mult = inv, row_scale = 1.f;
+    if (half) {
+      const f32x4_t am = *(LDS const f32x4_t*)(xamax + 8 * rl), an = *(LDS const f32x4_t*)(xamax + 8 * rl + 4);
+      const float amax = fmaxf(fmaxf(fmaxf(am[0], am[1]), fmaxf(am[2], am[3])),
+                               fmaxf(fmaxf(an[0], an[1]), fmaxf(an[2], an[3]))) * inv;
+      row_scale = amax > 0.f ? amax : 1.f;
+      mult = inv * (1.f / row_scale);
+    }
+    if (wave == k && g2 == 0 && row_wg0 + rl < p.rows) {
+      const int row = row_wg0 + rl;
+      const int i = row / p.H, hd = row - i * p.H;
+      const float lse = l_tot > 0.f ? (m_all[k] + __log2f(l_tot)) * kLn2 : -INFINITY;
+      const f32x2_t mt2 = *(LDS const f32x2_t*)(xtrue + 2 * rl);
+      const float mt = fmaxf(mt2[0], mt2[1]);
+      if (direct) {
+        const int64_t lo = r * p.lse_s0 + i * p.lse_s1 + hd * p.lse_s2;
+        if (p.out_wire) {
+          // (m, l): the largest score, and the denominator relative to it
+          p.lse[lo] = l_tot > 0.f ? mt * kLn2 : -INFINITY;
+          p.lse[lo + 1] = l_tot > 0.f ? l_tot * __builtin_amdgcn_exp2f(m_all[k] - mt) : 0.f;
+        } else {
+          p.lse[lo] = lse;
+        }
+      } else {
+        p.ws_lse[part * p.rows + row] = lse;
+        if (half) p.ws_scale[part * p.rows + row] = row_scale;
+        if (p.out_wire) p.ws_max[part * p.rows + row] = mt;
+      }
+    }
+    // the element offsets of this lane's two rows
+    int64_t off[2];
+    bool ok[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = row_wg0 + 32 * k + 16 * j + (lane & 15);
+      ok[j] = row < p.rows;
+      const int i = row / p.H, hd = row - i * p.H;
+      off[j] = direct ? r * p.out_s0 + i * p.out_s1 + hd * p.out_s2 : (part * p.rows + row) * kDLat;
+    }
+    if (half || (direct && p.out_wire)) {
+      uint16_t* const dst = half ? p.ws_o16 : p.out16;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const f32x16_t v = O[d][k];
+        uint32_t w[4][2];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const f32x4_t u = f32x4_t{v[4 * a], v[4 * a + 1], v[4 * a + 2], v[4 * a + 3]} * mult;
+          if (half) {
+            w[a][0] = pack_f16(u[0], u[1]);
+            w[a][1] = pack_f16(u[2], u[3]);
+          } else {
+            const u16x4_t b = f32x4_bf16(u);
+            w[a][0] = (uint32_t)b[0] | ((uint32_t)b[1] << 16);
+            w[a][1] = (uint32_t)b[2] | ((uint32_t)b[3] << 16);
+          }
+        }
+        u32x4_t u[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * b][0], w[2 * b + 1][0], false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * b][1], w[2 * b + 1][1], false, false);
+          u[b] = u32x4_t{s0[0], s1[0], s0[1], s1[1]};  // 8 columns from 16 b + 8 g2
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto s = __builtin_amdgcn_permlane16_swap(u[0][e], u[1][e], false, false);
+          u[0][e] = s[0];
+          u[1][e] = s[1];
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (ok[j]) *(u32x4_t*)(dst + off[j] + 64 * wave + 32 * d + 16 * (q & 1) + 8 * (q >> 1)) = u[j];
+      }
+    } else {
+      float* const dst = direct ? p.out : p.ws_o32;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const f32x16_t v = O[d][k];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          f32x4_t u[2];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[8 * b + e] * mult),
+                                                            __float_as_uint(v[8 * b + 4 + e] * mult), false, false);
+            u[0][e] = __uint_as_float(s[0]);
+            u[1][e] = __uint_as_float(s[1]);
+          }
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            if (ok[j]) *(f32x4_t*)(dst + off[j] + 64 * wave + 32 * d + 16 * b + 8 * (q & 1) + 4 * (q >> 1)) = u[j];
+        }
+      }
+    }
+  }
+}
+
 }  // namespace
 
 template <int KV, int SEL = kSelShared>
 static void launch_kv(const PartialParams& p, int grid, int row_groups, hipStream_t s) {
   if (row_groups == 2)
-    hipLaunchKernelGGL((partial_kernel<2, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((partial_kernel<KV, SEL>), dim3(grid), dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL((partial_kernel<1, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((tile64_kernel<KV, SEL>), dim3(grid), dim3(512), 0, s, p);
 }
 
 hipError_t launch_partial(const PartialParams& p, int R, int kv, int row_groups, int sel_kind,

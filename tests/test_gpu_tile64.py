@@ -1,0 +1,94 @@
+"""The 64-row kernel at the edges of its tiles, stages and pipeline, against
+the oracle: row counts around its 8-, 16- and 32-row groups, odd head counts
+(its query rows are loaded row by row), stage counts below and above the ring,
+strided query rows, and scores that keep raising the running maxima.
+
+Tolerances are the parity bar of gpu_helpers.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_01502_amd import mla, workloads as W
+from tests import gpu_helpers as G
+
+pytestmark = pytest.mark.gpu
+
+
+def _ref(w):
+    return oracle.partial(w.q_lat, w.q_pe, w.ckv, w.kpe, w.table, w.sel, w.scale, w.ckv_scale,
+                          w.kpe_scale, tokens=w.tokens)
+
+
+def _check(w, what, **kw):
+    print("case:", what, flush=True)
+    out, lse = G.run_partial(G.upload(w), w.scale, row_tile=64, tokens=w.tokens, **kw)
+    G.assert_parity(out, lse, *_ref(w), what)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp8split"])
+@pytest.mark.parametrize("mq,h", [(1, 1), (1, 8), (5, 3), (1, 17), (1, 31), (7, 7), (1, 64), (1, 65), (3, 43)])
+def test_row_edges(mq, h, kv):
+    w = W.random_case(900 + 7 * mq + h, R=2, Mq=mq, H=h, P=12, NB=9, K=3)
+    if kv != "bf16":
+        w = w.to_fp8(kv == "fp8")
+    _check(w, f"rows {mq}x{h} {kv}")
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp8split"])
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 64, 65, 95, 97, 191, 193, 225])
+def test_stage_counts_tokens(k, kv):
+    # 32 tokens a stage: one stage, a full ring and beyond it, ragged ends
+    w = W.random_case(930 + k, R=2, Mq=1, H=40, P=16, NB=11, K=k, tokens=True)
+    if kv != "bf16":
+        w = w.to_fp8(kv == "fp8")
+    _check(w, f"tokens {k} {kv}", n_splits=1)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("blocks", [0, 1, 2, 3, 4, 7])
+def test_stage_counts_blocks(blocks, kv):
+    w = W.random_case(960 + blocks, R=3, Mq=2, H=24, P=16, NB=11, K=8, n_valid=[blocks, 8, 0],
+                      pad_pattern="interleaved")
+    if kv != "bf16":
+        w = w.to_fp8()
+    _check(w, f"blocks {blocks} {kv}", n_splits=1)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_per_row_counters_past_the_query_rows(kv):
+    # so many logical blocks that the compaction's counters reach the place of
+    # the query rows (and, for fp8, past the ring)
+    w = W.random_case(980, R=1, Mq=64, H=1, P=64, NB=1100, K=6, per_row=True)
+    if kv != "bf16":
+        w = w.to_fp8()
+    _check(w, f"per-row counters {kv}", n_splits=1)
+
+
+@pytest.mark.parametrize("wire", [False, True])
+def test_strided_queries_and_rising_maxima(wire):
+    # blocks of growing magnitude: most stages raise some row's maximum by more
+    # than the rescale threshold; the queries are slices of wider tensors
+    w = W.random_case(990, R=2, Mq=3, H=10, P=20, NB=12, K=12)
+    for r in range(2):
+        w.sel[r] = np.arange(12)
+        for j in range(12):
+            b = w.table[r, j]
+            f = np.float32(0.25 * 1.45 ** j)
+            w.ckv[b] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(w.ckv[b]) * f)
+    t = G.upload(w)
+    wide = torch.zeros((2, 5, 13, 512 + 64), dtype=torch.bfloat16, device="cuda")
+    wide[:, 1:4, 2:12, :512] = t["q_lat"]
+    wide[:, 1:4, 2:12, 512:] = t["q_pe"]
+    ref_o, ref_l = _ref(w)
+    for ns in (1, 3):
+        print(f"case: strided wire={wire} splits={ns}", flush=True)
+        out, lse = mla.sparse_partial_attn(wide[:, 1:4, 2:12, :512], wide[:, 1:4, 2:12, 512:], t["ckv"],
+                                           t["kpe"], t["table"], t["sel"], w.scale, n_splits=ns,
+                                           row_tile=64, wire=wire)
+        torch.cuda.synchronize()
+        lse = lse.double().cpu().numpy()
+        if wire:
+            lse = lse[..., 0] + np.log(lse[..., 1])
+        G.assert_parity(out.double().cpu().numpy(), lse, ref_o, ref_l, f"wire={wire} splits={ns}")
