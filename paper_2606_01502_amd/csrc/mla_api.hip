@@ -423,6 +423,13 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     // are worth more than the shared block loads)
     p.tiles_fast = by_id && row_tiles >= 8 ? 1 : 0;
     p.row_tiles = (int32_t)row_tiles;
+    p.by_splits = mla::make_div(S);
+    p.by_tiles = mla::make_div(row_tiles);
+    p.by_H = mla::make_div(H);
+    p.by_jobs = mla::make_div(p.q_jobs);
+    p.by_rep = mla::make_div(p.q_rep);
+    p.by_K = mla::make_div(std::max<int64_t>(K, 1));
+    p.grid8 = (int32_t)(R * row_tiles * S % 8 ? 0 : R * row_tiles * S / 8);
     p.scale_log2 = (float)((double)scale * 1.4426950408889634074);
     p.out_wire = wire ? 1 : 0;
     p.out16 = (uint16_t*)out_lat->data;
@@ -473,6 +480,8 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
       c.ws_lse = p.ws_lse;
       c.ws_max = p.ws_max;
       c.R = (int32_t)R; c.S = (int32_t)S; c.Mq = (int32_t)Mq; c.H = (int32_t)H; c.rows = (int32_t)rows;
+      c.by_H = p.by_H;
+      c.by_rows = mla::make_div(rows);
       c.out_wire = p.out_wire;
       c.out16 = p.out16;
       c.out = p.out; c.out_s0 = p.out_s0; c.out_s1 = p.out_s1; c.out_s2 = p.out_s2;
@@ -746,6 +755,8 @@ mla_status_t mla_merge_partials_ex(const mla_tensor_t* const* out_lat,
     p.n_parts = n_parts;
     p.wire = wire ? 1 : 0;
     p.B = (int32_t)B; p.Mq = (int32_t)Mq; p.H = (int32_t)H;
+    p.by_H = mla::make_div(std::max<int64_t>(H, 1));
+    p.by_Mq = mla::make_div(std::max<int64_t>(Mq, 1));
     p.o_s0 = out_lat[0]->stride[0]; p.o_s1 = out_lat[0]->stride[1]; p.o_s2 = out_lat[0]->stride[2];
     p.l_s0 = out_lse[0]->stride[0]; p.l_s1 = out_lse[0]->stride[1]; p.l_s2 = out_lse[0]->stride[2];
     p.out = (float*)out->data;

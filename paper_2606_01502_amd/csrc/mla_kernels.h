@@ -17,6 +17,23 @@ constexpr int kMaxParts = 64;
 // rows (below it, as for a handful of rows, the shorter fp32 epilogue pays)
 constexpr int64_t kWsHalfMinBytes = 1ll << 20;
 
+// Division of 0 <= n < 2^31 by a divisor d >= 1 that the host knows: n m >> s
+// with s = 31 + ceil(log2 d), m = floor(2^s / d) + 1.  m d = 2^s + e with 0 < e
+// <= d <= 2^(s - 31), so n m / 2^s exceeds n / d by n e / (d 2^s) < 1 / d: the
+// floors agree.  (A division by a value the compiler does not know takes about
+// 30 dependent instructions; a 64-row work item started with five of them.)
+struct Div {
+  uint32_t d, m, s;
+};
+inline Div make_div(int64_t d) {
+  uint32_t l = 0;
+  while ((1ll << l) < d) ++l;
+  return Div{(uint32_t)d, (uint32_t)((1ull << (31 + l)) / (uint64_t)d + 1), 31 + l};
+}
+__host__ __device__ inline int div_by(int n, const Div& d) {
+  return (int)(((uint64_t)(uint32_t)n * d.m) >> d.s);
+}
+
 // Partial attention over one (job, row tile, slot range) per workgroup.
 struct PartialParams {
   const uint16_t* q_lat;  // bf16 bits
@@ -46,6 +63,10 @@ struct PartialParams {
   // work items numbered row tiles fastest (per-row selections split by
   // logical block, with enough row tiles that one split's tiles fill an XCD)
   int32_t tiles_fast;
+  // divisors: n_splits, row_tiles, H, q_jobs, q_rep, and K (per-row selections);
+  // grid8: workgroups / 8 when 8 divides them, else 0
+  Div by_splits, by_tiles, by_H, by_jobs, by_rep, by_K;
+  int32_t grid8;
   float scale_log2;  // softmax scale * log2(e)
   // destination: direct (n_splits == 1) or split-K workspace.  out_wire: the
   // bf16 wire form (Section 3.2): bf16 rows at out16 (element strides out_s*)
@@ -77,6 +98,7 @@ struct CombineParams {
   const float* ws_lse;
   const float* ws_max;  // the splits' largest scores (log2 units), wire form only
   int32_t R, S, Mq, H, rows;
+  Div by_H, by_rows;    // divisors
   int32_t out_wire;     // see PartialParams
   float* out;
   uint16_t* out16;
@@ -94,6 +116,7 @@ struct MergeParams {
   int32_t wire;
   int32_t n_parts;
   int32_t B, Mq, H;
+  Div by_H, by_Mq;  // divisors
   int64_t o_s0, o_s1, o_s2;
   int64_t l_s0, l_s1, l_s2;
   float* out;

@@ -21,9 +21,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const MergeParams p) {
   const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
   if (row >= n_rows) return;
   const int lane = threadIdx.x & 63;
-  const int b = row / (p.Mq * p.H);
-  const int rem = row - b * (p.Mq * p.H);
-  const int i = rem / p.H, h = rem - (rem / p.H) * p.H;
+  const int bi = div_by(row, p.by_H), h = row - bi * p.H;
+  const int b = div_by(bi, p.by_Mq), i = bi - b * p.Mq;
   const int64_t lo = b * p.l_s0 + i * p.l_s1 + h * p.l_s2;
   const int64_t oo = b * p.o_s0 + i * p.o_s1 + h * p.o_s2;
   f32x4_t acc0, acc1;
@@ -57,7 +56,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const CombineParams p
   const int grow = blk * kRowsPerBlock + (threadIdx.x >> 6);
   if (grow >= n_rows) return;
   const int lane = threadIdx.x & 63;
-  const int r = grow / p.rows;
+  const int r = div_by(grow, p.by_rows);
   const int row = grow - r * p.rows;
   combine_row(p, p.S, r, row, lane);
 }

@@ -611,15 +611,18 @@ __device__ __forceinline__ int compact_per_row(const PartialParams& p, int r, in
   LDS const uint16_t* cnt16 = (LDS const uint16_t*)smem;
   LDS int* wave_cnt = (LDS int*)(smem + L::kWaveCnt);
   LDS float* scales = (LDS float*)(smem + L::kScales);
-  const int n_ids = id0 < p.NB ? (p.NB - id0 + id_step - 1) / id_step : 0;
+  // (split by logical block: nslots is K and id_step n_splits; else id_step is 1)
+  auto row_of = [&](int e) { return p.split_by_id ? div_by(e, p.by_K) : e / nslots; };
+  auto steps = [&](int d) { return p.split_by_id ? div_by(d, p.by_splits) : d; };
+  const int n_ids = id0 < p.NB ? steps(p.NB - id0 + id_step - 1) : 0;
   const int n_words = (n_ids * n_i + 1) >> 1;
   for (int w = tid; w < n_words; w += L::kThreads) cnt[w] = 0u;
   lds_barrier();
   const int n_ent = n_i * nslots;
   for (int e = tid; e < n_ent; e += L::kThreads) {
-    const int ii = e / nslots, j = e - ii * nslots;
+    const int ii = row_of(e), j = e - ii * nslots;
     const int id = e == tid ? first_id : p.sel[r * p.sel_s0 + (int64_t)(i0 + ii) * p.sel_s1 + slot0 + j];
-    const int u = (id - id0) / id_step;
+    const int u = id >= id0 ? steps(id - id0) : 0;
     if (id >= id0 && id < p.NB && u * id_step == id - id0) {
       const int bb = p.table[r * p.table_s0 + id];
       if (bb >= 0 && bb < p.P) {
@@ -783,15 +786,25 @@ void partial_kernel(const PartialParams p) {
   // of the same residue class, which then meet in the L2 of one or two XCDs
   // instead of all eight (the query rows, read once per split, are what is
   // fetched more than once instead, the smaller of the two).
-  const int w_id = gridDim.x % 8 ? (int)blockIdx.x
-                                 : (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+  const int w_id = p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8);
   const bool tiles_fast = PR && p.tiles_fast;
-  const int s_idx = tiles_fast ? (w_id / p.row_tiles) % p.n_splits : w_id % p.n_splits;
-  const int rt = tiles_fast ? w_id % p.row_tiles : (w_id / p.n_splits) % p.row_tiles;
-  const int r_num = w_id / (p.n_splits * p.row_tiles);
+  int s_idx, rt, r_num;
+  if (tiles_fast) {
+    const int a = div_by(w_id, p.by_tiles);
+    rt = w_id - a * p.row_tiles;
+    r_num = div_by(a, p.by_splits);
+    s_idx = a - r_num * p.n_splits;
+  } else {
+    const int a = div_by(w_id, p.by_splits);
+    s_idx = w_id - a * p.n_splits;
+    r_num = div_by(a, p.by_tiles);
+    rt = a - r_num * p.row_tiles;
+  }
   // jobs that share q rows (r, r + q_jobs, ...) take consecutive numbers
-  const int r = p.q_rep > 1 ? (r_num % p.q_rep) * p.q_jobs + r_num / p.q_rep : r_num;
-  const int rq = r % p.q_jobs;  // the job's q rows
+  // (a job's q rows are rq, r mod q_jobs)
+  const int rep = p.q_rep > 1 ? div_by(r_num, p.by_rep) : 0;
+  const int r = p.q_rep > 1 ? (r_num - rep * p.q_rep) * p.q_jobs + rep : r_num;
+  const int rq = p.q_rep > 1 ? rep : r_num;
   const int slot0 = s_idx * p.slots_per_split;
   const int nslots = max(0, min(p.K - slot0, p.slots_per_split));
 
@@ -802,19 +815,19 @@ void partial_kernel(const PartialParams p) {
   LDS int* list = (LDS int*)(smem + L::kList);
   LDS float* scales = (LDS float*)(smem + L::kScales);
   LDS uint64_t* masks = (LDS uint64_t*)(smem + L::kMasks);
-  const int i0 = rt * kRowsWg / p.H;  // first query row of the tile
+  const int i0 = div_by(rt * kRowsWg, p.by_H);  // first query row of the tile
   // per-row selections: the query rows of the tile; split by logical block
   // (split s takes blocks s, s + S, ... from every slot), so that rows which
   // chose one block in different slots share its load, or by slot range when
   // a tile's slots may not fit one list
-  const int n_i = PR ? (min((rt + 1) * kRowsWg, p.rows) - 1) / p.H - i0 + 1 : 1;
+  const int n_i = PR ? div_by(min((rt + 1) * kRowsWg, p.rows) - 1, p.by_H) - i0 + 1 : 1;
   const int c_slot0 = PR && p.split_by_id ? 0 : slot0;
   const int c_nslots = PR && p.split_by_id ? p.K : nslots;
   // the slot id this thread compacts first
   int first_id = -1;
   if constexpr (PR) {
     if (tid < n_i * c_nslots) {
-      const int ii = tid / c_nslots, j = tid - ii * c_nslots;
+      const int ii = p.split_by_id ? div_by(tid, p.by_K) : tid / c_nslots, j = tid - ii * c_nslots;
       first_id = p.sel[r * p.sel_s0 + (int64_t)(i0 + ii) * p.sel_s1 + c_slot0 + j];
     }
   } else {
@@ -830,7 +843,7 @@ void partial_kernel(const PartialParams p) {
   for (int rg = 0; rg < RG; ++rg) {
     const int row = row_wg0 + wave * 16 * RG + rg * 16 + n16;
     if (row < p.rows) {
-      const int i = row / p.H, h = row - (row / p.H) * p.H;
+      const int i = div_by(row, p.by_H), h = row - i * p.H;
       const uint16_t* ql = p.q_lat + rq * p.ql_s0 + i * p.ql_s1 + h * p.ql_s2 + g * 8;
       const uint16_t* qp = p.q_pe + rq * p.qp_s0 + i * p.qp_s1 + h * p.qp_s2 + g * 8;
 #pragma unroll
@@ -900,7 +913,7 @@ void partial_kernel(const PartialParams p) {
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
     const int row = row_wg0 + wave * 16 * RG + rg * 16 + n16;
-    row_bit[rg] = PR ? min(max(row / p.H - i0, 0), 63) : 0;
+    row_bit[rg] = PR ? min(max(div_by(row, p.by_H) - i0, 0), 63) : 0;
   }
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
@@ -1300,7 +1313,7 @@ void partial_kernel(const PartialParams p) {
     if (!half) {
       if (g == 0 && row < p.rows) {
         if (direct) {
-          const int i = row / p.H, hd = row - (row / p.H) * p.H;
+          const int i = div_by(row, p.by_H), hd = row - i * p.H;
           const int64_t lo = r * p.lse_s0 + i * p.lse_s1 + hd * p.lse_s2;
           if (p.out_wire) {
             // (m, l): the largest score, and the denominator relative to it
@@ -1317,7 +1330,7 @@ void partial_kernel(const PartialParams p) {
       }
       if (row < p.rows && direct && p.out_wire) {
         // bf16 rows: 8-byte runs per row and instruction
-        const int i = row / p.H, hd = row - (row / p.H) * p.H;
+        const int i = div_by(row, p.by_H), hd = row - i * p.H;
         uint16_t* dst = p.out16 + r * p.out_s0 + i * p.out_s1 + hd * p.out_s2;
 #pragma unroll
         for (int dt = 0; dt < 32; ++dt) {
@@ -1328,7 +1341,7 @@ void partial_kernel(const PartialParams p) {
       } else if (row < p.rows) {
         float* dst;
         if (direct) {
-          const int i = row / p.H, hd = row - (row / p.H) * p.H;
+          const int i = div_by(row, p.by_H), hd = row - i * p.H;
           dst = p.out + r * p.out_s0 + i * p.out_s1 + hd * p.out_s2;
         } else {
           dst = p.ws_o32 + (part * p.rows + row) * kDLat;
@@ -1507,6 +1520,14 @@ __device__ __forceinline__ const T* uniform(const T* a) {
   return (const T*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
+// 1 / v for finite v > 0 that is not denormal, to within a rounding of the last
+// bit (the hardware's reciprocal and one Newton step, 3 instructions; the
+// division takes a dozen dependent ones).
+__device__ __forceinline__ float recip(float v) {
+  const float r = __builtin_amdgcn_rcpf(v);
+  return __builtin_fmaf(__builtin_fmaf(-v, r, 1.f), r, r);
+}
+
 // The larger of lanes l and l ^ 32.
 __device__ __forceinline__ float xor32_max(float v) {
   const uint32_t u = __float_as_uint(v);
@@ -1644,14 +1665,24 @@ void tile64_kernel(const PartialParams p) {
   const int n16 = lane & 15, g = lane >> 4;  // S^T: row (or token) and dim group
   const int n32 = lane & 31, g2 = lane >> 5;  // O^T: row (or column) and token group
 
-  const int w_id = gridDim.x % 8 ? (int)blockIdx.x
-                                 : (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+  const int w_id = p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8);
   const bool tiles_fast = PR && p.tiles_fast;
-  const int s_idx = tiles_fast ? (w_id / p.row_tiles) % p.n_splits : w_id % p.n_splits;
-  const int rt = tiles_fast ? w_id % p.row_tiles : (w_id / p.n_splits) % p.row_tiles;
-  const int r_num = w_id / (p.n_splits * p.row_tiles);
-  const int r = p.q_rep > 1 ? (r_num % p.q_rep) * p.q_jobs + r_num / p.q_rep : r_num;
-  const int qj = r % p.q_jobs;  // the job's query rows
+  int s_idx, rt, r_num;
+  if (tiles_fast) {
+    const int a = div_by(w_id, p.by_tiles);
+    rt = w_id - a * p.row_tiles;
+    r_num = div_by(a, p.by_splits);
+    s_idx = a - r_num * p.n_splits;
+  } else {
+    const int a = div_by(w_id, p.by_splits);
+    s_idx = w_id - a * p.n_splits;
+    r_num = div_by(a, p.by_tiles);
+    rt = a - r_num * p.row_tiles;
+  }
+  // (a job's q rows are qj, r mod q_jobs)
+  const int rep = p.q_rep > 1 ? div_by(r_num, p.by_rep) : 0;
+  const int r = p.q_rep > 1 ? (r_num - rep * p.q_rep) * p.q_jobs + rep : r_num;
+  const int qj = p.q_rep > 1 ? rep : r_num;
   const int slot0 = s_idx * p.slots_per_split;
   const int nslots = max(0, min(p.K - slot0, p.slots_per_split));
 
@@ -1662,14 +1693,14 @@ void tile64_kernel(const PartialParams p) {
   LDS float* const xmax = (LDS float*)(smem + L::kX);
   LDS uint8_t* const flags = smem + L::kFlags;
   const int row_wg0 = rt * 64;
-  const int i0 = row_wg0 / p.H;
-  const int n_i = PR ? (min(row_wg0 + 64, p.rows) - 1) / p.H - i0 + 1 : 1;
+  const int i0 = div_by(row_wg0, p.by_H);
+  const int n_i = PR ? div_by(min(row_wg0 + 64, p.rows) - 1, p.by_H) - i0 + 1 : 1;
   const int c_slot0 = PR && p.split_by_id ? 0 : slot0;
   const int c_nslots = PR && p.split_by_id ? p.K : nslots;
   int first_id = -1;
   if constexpr (PR) {
     if (tid < n_i * c_nslots) {
-      const int ii = tid / c_nslots, j = tid - ii * c_nslots;
+      const int ii = p.split_by_id ? div_by(tid, p.by_K) : tid / c_nslots, j = tid - ii * c_nslots;
       first_id = p.sel[r * p.sel_s0 + (int64_t)(i0 + ii) * p.sel_s1 + c_slot0 + j];
     }
   } else {
@@ -1681,7 +1712,7 @@ void tile64_kernel(const PartialParams p) {
   auto issue_q = [&]() {
     const int row0 = row_wg0 + 8 * wave;
     const int rc = min(row0, p.rows - 1);
-    const int qi = __builtin_amdgcn_readfirstlane(rc / p.H);
+    const int qi = __builtin_amdgcn_readfirstlane(div_by(rc, p.by_H));
     int qh = rc - qi * p.H;
     const uint16_t* ql = p.q_lat + (qj * p.ql_s0 + qi * p.ql_s1 + qh * p.ql_s2);
     const int64_t wrap = p.ql_s1 - (int64_t)(p.H - 1) * p.ql_s2;
@@ -1699,7 +1730,7 @@ void tile64_kernel(const PartialParams p) {
     }
     const int t = 8 * wave + (lane >> 3);
     const int row = min(row_wg0 + t, p.rows - 1);
-    const int i = row / p.H, h = row - i * p.H;
+    const int i = div_by(row, p.by_H), h = row - i * p.H;
     const int c = (lane & 7) ^ rope_key32<false>(t);
     const uint16_t* src = p.q_pe + (qj * p.qp_s0 + i * p.qp_s1 + h * p.qp_s2) + 8 * c;
     Issue32<false, false>::go64((const uint8_t*)src, lds0 + L::kQ + 65536 + wave * 1024);
@@ -1774,8 +1805,13 @@ void tile64_kernel(const PartialParams p) {
   // of row 16 rq + n16: the running maximum, the sum and largest score over this
   // lane's tokens; m_all: the maxima of rows n32 and 32 + n32
   float m_run = -INFINITY, l_run = 0.f, m_true = -INFINITY;
+  // bf16 caches: the sum of the weights as rounded for the value product, which
+  // normalises O.  A row's output is then an average with weights that sum to 1,
+  // exact where one token holds all the weight (the sum of unrounded weights,
+  // l_run, makes the lse).
+  float l_norm = 0.f;
   float m_all[2] = {-INFINITY, -INFINITY};
-  const int row_bit = PR ? min(max((row_wg0 + 16 * rq + n16) / p.H - i0, 0), 63) : 0;
+  const int row_bit = PR ? min(max(div_by(row_wg0 + 16 * rq + n16, p.by_H) - i0, 0), 63) : 0;
 
   // loop-invariant LDS addresses, less the stage
   constexpr int kRopeReads = FP8 ? 1 : 2, kReads = FP8 ? 9 : 18;
@@ -1822,7 +1858,7 @@ void tile64_kernel(const PartialParams p) {
   // a step: it publishes stage i + 1, the weights of stage i and the requests
   // to raise a maximum.
   f32x4_t sacc, pacc, x;
-  float psum = 0.f;
+  float psum = 0.f, pnorm = 0.f;
   bool on = true;                // of stage x: whether the row attends it
   float v_mult = 1.f;            // of stage x: the fp8 value scale
   int x_stage = 0;
@@ -1844,7 +1880,12 @@ void tile64_kernel(const PartialParams p) {
     psum = (e[0] + e[1]) + (e[2] + e[3]);
     if constexpr (FP8 && TOK) e *= tok_scale4(0, x_stage);
     else if constexpr (FP8) e *= v_mult;
-    *(LDS u16x4_t*)(pbuf + ((x_stage & 1) << 12) + p_put) = f32x4_bf16(e);
+    const u16x4_t w = f32x4_bf16(e);
+    *(LDS u16x4_t*)(pbuf + ((x_stage & 1) << 12) + p_put) = w;
+    if constexpr (!FP8) {
+      auto f = [](uint16_t b) { return __uint_as_float((uint32_t)b << 16); };
+      pnorm = (f(w[0]) + f(w[1])) + (f(w[2]) + f(w[3]));
+    }
   };
   // Softmax of a stage over this wave's 16 rows x 16 tokens, in parts.  The
   // scores, log2 units: the products are rounded before a maximum is taken off
@@ -2029,8 +2070,7 @@ void tile64_kernel(const PartialParams p) {
         lds_barrier();
       }
       // the new maximum of a row and the factor of what was summed under the old one
-      auto raise = [&](int row, float& m) -> float {
-        const f32x2_t b = *(LDS const f32x2_t*)(xmax + 2 * row);
+      auto raise = [&](f32x2_t b, float& m) -> float {
         const float bm = fmaxf(b[0], b[1]);
         float alpha = 1.f;
         if (bm > m + kTau) {
@@ -2039,18 +2079,22 @@ void tile64_kernel(const PartialParams p) {
         }
         return alpha;
       };
-      l_run *= raise(16 * rq + n16, m_run);
+      const f32x2_t b = *(LDS const f32x2_t*)(xmax + 2 * (16 * rq + n16));
+      const f32x2_t b0 = *(LDS const f32x2_t*)(xmax + 2 * n32), b1 = *(LDS const f32x2_t*)(xmax + 2 * (32 + n32));
+      __builtin_amdgcn_sched_barrier(0);  // one trip to LDS for all
+      const float own = raise(b, m_run);
+      l_run *= own;
+      l_norm *= own;
       put_p();
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        alpha[k] = raise(32 * k + n32, m_all[k]);
-        any |= __ballot(alpha[k] != 1.f) != 0;
-      }
+      alpha[0] = raise(b0, m_all[0]);
+      alpha[1] = raise(b1, m_all[1]);
+      any = __ballot(alpha[0] != 1.f || alpha[1] != 1.f) != 0;
       lds_barrier();
       pload(i, 0);
     }
     scale_all(O, alpha, any);
     l_run += psum;
+    l_norm += FP8 ? psum : pnorm;
   };
   // O^T[dim][row] += V^T . P^T over this wave's 64 columns and stage i.
   // kSoft: all but the last fragment, with the softmax of stage i + 1
@@ -2117,11 +2161,14 @@ void tile64_kernel(const PartialParams p) {
   lds_barrier();  // every wave is done with the last block's weights
   LDS float* const xsum = (LDS float*)pbuf;       // [64][2]
   LDS float* const xtrue = xsum + 128;            // [64][2]
-  LDS float* const xamax = xtrue + 128;           // [64][8]
+  LDS float* const xnorm = xtrue + 128;           // [64][2]
+  LDS float* const xamax = xnorm + 128;           // [64][8]
   {
     const float l = xor_sum(l_run);
+    const float ln = xor_sum(l_norm);
     const float mt = xor_max(m_true);
     if (g == 0) {
+      xnorm[(16 * rq + n16) * 2 + th] = ln;
       xsum[(16 * rq + n16) * 2 + th] = l;
       xtrue[(16 * rq + n16) * 2 + th] = mt;
     }
@@ -2141,45 +2188,59 @@ void tile64_kernel(const PartialParams p) {
     }
   }
   lds_barrier();
+  // the rows' statistics, both halves before the first store (their LDS trips overlap)
+  float mult[2];
+  {
+    f32x2_t ls[2], lw[2];
+    f32x4_t am[2], an[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int rl = 32 * k + n32;
+      ls[k] = *(LDS const f32x2_t*)(xsum + 2 * rl);
+      lw[k] = *(LDS const f32x2_t*)(xnorm + 2 * rl);
+      am[k] = *(LDS const f32x4_t*)(xamax + 8 * rl);
+      an[k] = *(LDS const f32x4_t*)(xamax + 8 * rl + 4);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int rl = 32 * k + n32, row = row_wg0 + rl;
+      const float l_tot = ls[k][0] + ls[k][1];
+      mult[k] = l_tot > 0.f ? recip(lw[k][0] + lw[k][1]) : 0.f;
+      float row_scale = 1.f;
+      if (half) {
+        const float amax = fmaxf(fmaxf(fmaxf(am[k][0], am[k][1]), fmaxf(am[k][2], am[k][3])),
+                                 fmaxf(fmaxf(an[k][0], an[k][1]), fmaxf(an[k][2], an[k][3]))) * mult[k];
+        row_scale = amax > 0.f ? amax : 1.f;
+        mult[k] *= 1.f / row_scale;
+      }
+      if (wave == k && g2 == 0 && row < p.rows) {
+        const float lse = l_tot > 0.f ? (m_all[k] + __log2f(l_tot)) * kLn2 : -INFINITY;
+        const f32x2_t mt2 = *(LDS const f32x2_t*)(xtrue + 2 * rl);
+        const float mt = fmaxf(mt2[0], mt2[1]);
+        if (direct) {
+          const int i = div_by(row, p.by_H), hd = row - i * p.H;
+          const int64_t lo = r * p.lse_s0 + i * p.lse_s1 + hd * p.lse_s2;
+          if (p.out_wire) {
+            // (m, l): the largest score, and the denominator relative to it
+            p.lse[lo] = l_tot > 0.f ? mt * kLn2 : -INFINITY;
+            p.lse[lo + 1] = l_tot > 0.f ? l_tot * __builtin_amdgcn_exp2f(m_all[k] - mt) : 0.f;
+          } else {
+            p.lse[lo] = lse;
+          }
+        } else {
+          p.ws_lse[part * p.rows + row] = lse;
+          if (half) p.ws_scale[part * p.rows + row] = row_scale;
+          if (p.out_wire) p.ws_max[part * p.rows + row] = mt;
+        }
+      }
+    }
+  }
   // A lane holds 4 neighbouring columns of row 32 k + n32 at a time, 8 apart;
   // swaps between lanes l, l ^ 16 (and l, l ^ 32 for 16-bit rows) give each
   // store instruction 64-byte runs of 16 rows: row 16 j + (lane & 15) of half k.
   const int q = lane >> 4;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    const int rl = 32 * k + n32;
-    const f32x2_t ls = *(LDS const f32x2_t*)(xsum + 2 * rl);
-    const float l_tot = ls[0] + ls[1];
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    float mult = inv, row_scale = 1.f;
-    if (half) {
-      const f32x4_t am = *(LDS const f32x4_t*)(xamax + 8 * rl), an = *(LDS const f32x4_t*)(xamax + 8 * rl + 4);
-      const float amax = fmaxf(fmaxf(fmaxf(am[0], am[1]), fmaxf(am[2], am[3])),
-                               fmaxf(fmaxf(an[0], an[1]), fmaxf(an[2], an[3]))) * inv;
-      row_scale = amax > 0.f ? amax : 1.f;
-      mult = inv * (1.f / row_scale);
-    }
-    if (wave == k && g2 == 0 && row_wg0 + rl < p.rows) {
-      const int row = row_wg0 + rl;
-      const int i = row / p.H, hd = row - i * p.H;
-      const float lse = l_tot > 0.f ? (m_all[k] + __log2f(l_tot)) * kLn2 : -INFINITY;
-      const f32x2_t mt2 = *(LDS const f32x2_t*)(xtrue + 2 * rl);
-      const float mt = fmaxf(mt2[0], mt2[1]);
-      if (direct) {
-        const int64_t lo = r * p.lse_s0 + i * p.lse_s1 + hd * p.lse_s2;
-        if (p.out_wire) {
-          // (m, l): the largest score, and the denominator relative to it
-          p.lse[lo] = l_tot > 0.f ? mt * kLn2 : -INFINITY;
-          p.lse[lo + 1] = l_tot > 0.f ? l_tot * __builtin_amdgcn_exp2f(m_all[k] - mt) : 0.f;
-        } else {
-          p.lse[lo] = lse;
-        }
-      } else {
-        p.ws_lse[part * p.rows + row] = lse;
-        if (half) p.ws_scale[part * p.rows + row] = row_scale;
-        if (p.out_wire) p.ws_max[part * p.rows + row] = mt;
-      }
-    }
     // the element offsets of this lane's two rows
     int64_t off[2];
     bool ok[2];
@@ -2187,8 +2248,12 @@ void tile64_kernel(const PartialParams p) {
     for (int j = 0; j < 2; ++j) {
       const int row = row_wg0 + 32 * k + 16 * j + (lane & 15);
       ok[j] = row < p.rows;
-      const int i = row / p.H, hd = row - i * p.H;
-      off[j] = direct ? r * p.out_s0 + i * p.out_s1 + hd * p.out_s2 : (part * p.rows + row) * kDLat;
+      if (direct) {
+        const int i = div_by(row, p.by_H), hd = row - i * p.H;
+        off[j] = r * p.out_s0 + i * p.out_s1 + hd * p.out_s2;
+      } else {
+        off[j] = (part * p.rows + row) * kDLat;
+      }
     }
     if (half || (direct && p.out_wire)) {
       uint16_t* const dst = half ? p.ws_o16 : p.out16;
@@ -2198,7 +2263,7 @@ void tile64_kernel(const PartialParams p) {
         uint32_t w[4][2];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const f32x4_t u = f32x4_t{v[4 * a], v[4 * a + 1], v[4 * a + 2], v[4 * a + 3]} * mult;
+          const f32x4_t u = f32x4_t{v[4 * a], v[4 * a + 1], v[4 * a + 2], v[4 * a + 3]} * mult[k];
           if (half) {
             w[a][0] = pack_f16(u[0], u[1]);
             w[a][1] = pack_f16(u[2], u[3]);
@@ -2235,8 +2300,8 @@ void tile64_kernel(const PartialParams p) {
           f32x4_t u[2];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[8 * b + e] * mult),
-                                                            __float_as_uint(v[8 * b + 4 + e] * mult), false, false);
+            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[8 * b + e] * mult[k]),
+                                                            __float_as_uint(v[8 * b + 4 + e] * mult[k]), false, false);
             u[0][e] = __uint_as_float(s[0]);
             u[1][e] = __uint_as_float(s[1]);
           }

@@ -245,7 +245,7 @@ __device__ __forceinline__ float merge_parts(int n, LseAt lse_at, RowAt row_at, 
 template <typename P>
 __device__ __forceinline__ void combine_row(const P& p, int S, int r, int row, int lane) {
   const int64_t base = (int64_t)r * S * p.rows + row;  // split j of (r, row) at base + j*rows
-  const int i = row / p.H, h = row - (row / p.H) * p.H;
+  const int i = div_by(row, p.by_H), h = row - i * p.H;
   const int64_t oo = r * p.out_s0 + i * p.out_s1 + h * p.out_s2;
   auto lse_at = [&](int j) { return p.ws_lse[base + (int64_t)j * p.rows]; };
   auto row16 = [&](int j) { return p.ws_o16 + (base + (int64_t)j * p.rows) * kDLat; };
