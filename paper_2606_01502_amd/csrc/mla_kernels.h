@@ -125,7 +125,7 @@ struct MergeParams {
   int64_t ol_s0, ol_s1, ol_s2;
 };
 
-// FETCH-side copy kernels: one workgroup moves 64 tokens of one layer.
+// FETCH-side copy kernels: one workgroup moves 32 tokens of one layer.
 struct FetchParams {
   // splice: chunk rows [L][n][D] -> pool rows; gather: pool rows -> out rows [L][K][D]
   const uint16_t* src_ckv;

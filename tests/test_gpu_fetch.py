@@ -129,3 +129,26 @@ def test_splice_host_checks():
     assert e.value.status == mla.MLA_ERR_INVALID_ARGUMENT
     with pytest.raises(mla.MlaError):
         mla.fetch_splice(chunk, chunk_k, _bf16(ckv), _bf16(kpe), table, 0, 0, pairing=2)
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 95, 97])
+def test_copies_at_the_edges_of_a_workgroup(n):
+    """Workgroups move 32 tokens of a layer: counts on either side of that, and
+    a splice that starts inside a block, with one block skipped."""
+    print(f"case: copies n={n}", flush=True)
+    ckv, kpe = _pools(860 + n, 2, 12)
+    rng = np.random.default_rng(870 + n)
+    sel = rng.integers(0, 10 * 64, n).astype(np.int32)
+    sel[-1] = -1                             # the last slot of the last workgroup: a zero row
+    table = rng.permutation(12)[:10].astype(np.int32)
+    oc = torch.full((2, n + 1, 512), 7.0, dtype=torch.bfloat16, device=G.device())
+    ok = torch.full((2, n + 1, 64), 7.0, dtype=torch.bfloat16, device=G.device())
+    got_c, got_k = oc.view(-1)[:2 * n * 512].view(2, n, 512), ok.view(-1)[:2 * n * 64].view(2, n, 64)
+    mla.fetch_gather(_bf16(ckv), _bf16(kpe), _i32(table), _i32(sel), out_ckv=got_c, out_kpe=got_k)
+    torch.cuda.synchronize()
+    rc, rk = F.gather(ckv, kpe, table, sel)
+    assert np.array_equal(_bits(got_c), rc) and np.array_equal(_bits(got_k), rk)
+    # nothing past the last row
+    assert bool((oc.view(-1)[2 * n * 512:] == 7).all()) and bool((ok.view(-1)[2 * n * 64:] == 7).all())
+    for pairing in (0, 1):
+        _check_splice(n, 2, 45, 4097, pairing, 10000.0, 880 + n, bad_entry=n > 32)
