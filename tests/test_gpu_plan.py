@@ -1,0 +1,72 @@
+"""Automatic plans (splits and row tile chosen by the library) around whole
+waves of workgroups, against one split and against the oracle on sampled jobs:
+the split rows of one call are rounded to fp16 or kept in fp32, so two plans
+agree to the library's parity bound."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_01502_amd import mla
+from tests import gpu_helpers as G
+
+pytestmark = pytest.mark.gpu
+
+SCALE = 576 ** -0.5
+
+
+def _inputs(R, Mq, H, K, NB, tokens, per_row, seed):
+    g = torch.Generator(device=G.device())
+    g.manual_seed(seed)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device=G.device()).bfloat16()
+
+    P = 96
+    table = torch.stack([torch.randperm(P, generator=g, device=G.device())[:NB] for _ in range(R)])
+    n_ids = NB * 64 if tokens else NB
+    lists = R * Mq if per_row else R
+    sel = torch.stack([torch.randperm(n_ids, generator=g, device=G.device())[:K]
+                       for _ in range(lists)])
+    if per_row:
+        sel = sel.view(R, Mq, K)
+    return dict(q_lat=normal(R, Mq, H, 512), q_pe=normal(R, Mq, H, 64), ckv=normal(P, 64, 512) * 0.5,
+                kpe=normal(P, 64, 64) * 0.5, table=table.int(), sel=sel.int())
+
+
+# (jobs, query rows, heads, slots, blocks of the table): grids that just fit a
+# wave of 256 workgroups, just pass it, and pass two and three
+@pytest.mark.parametrize("R,Mq,H,K,NB,tokens,per_row", [
+    (20, 1, 128, 40, 40, False, False), (86, 1, 64, 12, 40, False, False),
+    (128, 1, 16, 9, 40, False, False), (129, 1, 16, 9, 40, False, False),
+    (257, 1, 16, 24, 40, False, False), (300, 1, 128, 10, 40, False, False),
+    (24, 1, 128, 700, 40, True, False), (130, 1, 64, 129, 8, True, False),
+    (1, 100, 16, 16, 64, False, True), (1, 130, 20, 6, 90, False, True)])
+def test_automatic_plans(R, Mq, H, K, NB, tokens, per_row):
+    print(f"case: plan R={R} Mq={Mq} H={H} K={K} tokens={tokens} per_row={per_row}", flush=True)
+    t = _inputs(R, Mq, H, K, NB, tokens, per_row, 7000 + R + K)
+    args = (t["q_lat"], t["q_pe"], t["ckv"], t["kpe"], t["table"], t["sel"], SCALE)
+    out, lse = mla.sparse_partial_attn(*args, tokens=tokens)
+    ref_o, ref_l = mla.sparse_partial_attn(*args, tokens=tokens, n_splits=1)
+    torch.cuda.synchronize()
+    # weights are rounded to bf16 (2^-9) and split rows to fp16 (2^-11 of the
+    # row's largest), in each of the two plans
+    err = (out - ref_o).abs().amax(-1) / ref_o.abs().amax(-1)
+    assert float(err.max()) <= 2 * (2 ** -8 + 2 ** -11), float(err.max())
+    assert float((lse - ref_l).abs().max()) <= 1e-4
+    # float64 attention of the first and the last job's last query row
+    for r in (0, R - 1):
+        ids = t["sel"][r, Mq - 1] if per_row else t["sel"][r]
+        if tokens:
+            blk = t["table"][r][(ids // 64).long()].long()
+            k_lat, k_pe = t["ckv"][blk, (ids % 64).long()], t["kpe"][blk, (ids % 64).long()]
+        else:
+            blk = t["table"][r][ids.long()].long()
+            k_lat, k_pe = t["ckv"][blk].reshape(-1, 512), t["kpe"][blk].reshape(-1, 64)
+        k_lat, k_pe = k_lat.double().cpu(), k_pe.double().cpu()
+        s = (t["q_lat"][r, Mq - 1].double().cpu() @ k_lat.T + t["q_pe"][r, Mq - 1].double().cpu() @ k_pe.T) * SCALE
+        want_l = torch.logsumexp(s, -1)
+        want = torch.softmax(s, -1) @ k_lat
+        got = out[r, Mq - 1].double().cpu()
+        e = (got - want).abs().amax(-1) / want.abs().amax(-1)
+        assert float(e.max()) <= 2 ** -8 + 2 ** -11, float(e.max())
+        assert float((lse[r, Mq - 1].double().cpu() - want_l).abs().max()) <= 1e-4
