@@ -13,8 +13,7 @@
 // its first store.  2048 tokens x 27 layers, both in turn on three sets of
 // buffers: 53.0 -> 44.2 us (5.8 TB/s); 4096 x 61 layers 233 -> 198.  Spliced
 // rows stored past the caches too: 43.5 and 177, but attention over them,
-// layer by layer, takes 394 us for 375; the payload
-// so stored: 52.1.
+// layer by layer, takes 394 us for 375; the payload so stored: 52.1.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>

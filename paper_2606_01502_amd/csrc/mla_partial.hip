@@ -1414,11 +1414,19 @@ void partial_kernel(const PartialParams p) {
 // In a pipeline over 32-token stages: while the value products of stage i run,
 // the softmax of stage i + 1 is computed between them, with one barrier a
 // stage.  Measured against 4 waves of 16 rows, each with all keys and values
-// (partial call, us): one request x 128 heads x 32 blocks 17.2 -> 14.6, 16
-// requests x 64 rows x 32 blocks 23.5 -> 20.7, 256 requesters x 16 heads on 32
-// blocks 35.8 -> 30.4, 64 of them with 32 of 128 blocks each 34.7 -> 29.5, fp8
-// with 120 rows x 47 blocks 28.1 -> 24.1, 16 rows x 2 blocks 9.8 -> 9.3.  Four
+// (partial call, us): one request x 128 heads x 32 blocks 17.2 -> 14.4, 16
+// requests x 64 rows x 32 blocks 23.5 -> 20.4, 256 requesters x 16 heads on 32
+// blocks 35.8 -> 30.4, 64 of them with 32 of 128 blocks each 34.7 -> 29.9, fp8
+// with 120 rows x 47 blocks 28.1 -> 24.2, 16 rows x 2 blocks 9.8 -> 8.0.  Four
 // waves with this split of the work: 16.2, 21.7, 31.9, 32.7, 24.9 and 11.1.
+//
+// Jobs of at most 32 rows take one row half (NK = 1): half the value products
+// and half the weights' reads, and the scores by the first four waves alone,
+// one on each SIMD, while the others go on to their value reads.  The tile was
+// bound by issue and products for rows that are not there: 16 rows x 2 blocks
+// 8.96 -> 8.01 us, 64 jobs of 16 rows x 2048 tokens 55.4 -> 37.5 (fp8 32.7 ->
+// 29.4), x 32 blocks of fp8 30.3 -> 25.9, 32 jobs x 256 blocks 120 -> 113 (fp8
+// 100 -> 77), bit-identical.  33 to 48 rows keep both halves.
 //
 // LDS of a 64-row tile: a ring of 32-token stages (half a block: bf16 four of
 // 36 KiB, fp8 six of 18 KiB of codes), the block list with its fp8 factors and
@@ -1507,6 +1515,17 @@ __device__ __forceinline__ void scale_all(f32x16_t (&O)[2][2], const float (&alp
       "s_nop 2\n.Lkeep%=:"
       : "+{v[0:15]}"(O[0][0]), "+{v[16:31]}"(O[0][1]), "+{v[32:47]}"(O[1][0]), "+{v[48:63]}"(O[1][1])
       : "v"(alpha[0]), "v"(alpha[1]), "s"(__builtin_amdgcn_readfirstlane(any))
+      : "scc");
+}
+__device__ __forceinline__ void scale_all(f32x16_t (&O)[2][1], const float (&alpha)[1], int any) {
+  asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+      MLA_MUL4(0, 1, 2, 3, "%2") MLA_MUL4(4, 5, 6, 7, "%2")
+      MLA_MUL4(8, 9, 10, 11, "%2") MLA_MUL4(12, 13, 14, 15, "%2")
+      MLA_MUL4(16, 17, 18, 19, "%2") MLA_MUL4(20, 21, 22, 23, "%2")
+      MLA_MUL4(24, 25, 26, 27, "%2") MLA_MUL4(28, 29, 30, 31, "%2")
+      "s_nop 2\n.Lkeep%=:"
+      : "+{v[0:15]}"(O[0][0]), "+{v[16:31]}"(O[1][0])
+      : "v"(alpha[0]), "s"(__builtin_amdgcn_readfirstlane(any))
       : "scc");
 }
 #undef MLA_MUL4
@@ -1645,7 +1664,7 @@ struct Issue32 {
   }
 };
 
-template <int KV, int SEL>
+template <int KV, int SEL, int NK>  // NK: row halves of 32 rows
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tile64_kernel(const PartialParams p) {
   constexpr bool FP8 = KV != kKvBf16;
@@ -1660,8 +1679,11 @@ void tile64_kernel(const PartialParams p) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rq = wave & 3;   // S^T: rows 16 rq .. 16 rq + 15 of the tile
-  const int th = wave >> 2;  // S^T: tokens 16 th .. 16 th + 15 of a stage
+  // S^T: rows 16 rq .. 16 rq + 15 of the tile, tokens 16 th .. 16 th + 15 of a
+  // stage (one row half: the first four waves only, one on each SIMD)
+  const int rq = NK == 2 ? wave & 3 : wave & 1;
+  const int th = NK == 2 ? wave >> 2 : (wave >> 1) & 1;
+  const bool act = NK == 2 || wave < 4;
   const int n16 = lane & 15, g = lane >> 4;  // S^T: row (or token) and dim group
   const int n32 = lane & 31, g2 = lane >> 5;  // O^T: row (or column) and token group
 
@@ -1710,6 +1732,7 @@ void tile64_kernel(const PartialParams p) {
   // query rows to LDS: wave w loads rows 8w .. 8w+7 of the tile (rows past the
   // job's end repeat its last row; they are never stored)
   auto issue_q = [&]() {
+    if (!act) return;
     const int row0 = row_wg0 + 8 * wave;
     const int rc = min(row0, p.rows - 1);
     const int qi = __builtin_amdgcn_readfirstlane(div_by(rc, p.by_H));
@@ -1797,11 +1820,11 @@ void tile64_kernel(const PartialParams p) {
   }
 
   // O^T: column tile d (columns 64 wave + 32 d ..) x row half
-  f32x16_t O[2][2];
+  f32x16_t O[2][NK];
 #pragma unroll
   for (int d = 0; d < 2; ++d)
 #pragma unroll
-    for (int k = 0; k < 2; ++k) O[d][k] = f32x16_t{};
+    for (int k = 0; k < NK; ++k) O[d][k] = f32x16_t{};
   // of row 16 rq + n16: the running maximum, the sum and largest score over this
   // lane's tokens; m_all: the maxima of rows n32 and 32 + n32
   float m_run = -INFINITY, l_run = 0.f, m_true = -INFINITY;
@@ -1810,7 +1833,9 @@ void tile64_kernel(const PartialParams p) {
   // exact where one token holds all the weight (the sum of unrounded weights,
   // l_run, makes the lse).
   float l_norm = 0.f;
-  float m_all[2] = {-INFINITY, -INFINITY};
+  float m_all[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) m_all[k] = -INFINITY;
   const int row_bit = PR ? min(max(div_by(row_wg0 + 16 * rq + n16, p.by_H) - i0, 0), 63) : 0;
 
   // loop-invariant LDS addresses, less the stage
@@ -1857,7 +1882,7 @@ void tile64_kernel(const PartialParams p) {
   // stage i - 1 + kNum go to the ring slot that stage i - 1 left.  One barrier
   // a step: it publishes stage i + 1, the weights of stage i and the requests
   // to raise a maximum.
-  f32x4_t sacc, pacc, x;
+  f32x4_t sacc{}, pacc{}, x{};
   float psum = 0.f, pnorm = 0.f;
   bool on = true;                // of stage x: whether the row attends it
   float v_mult = 1.f;            // of stage x: the fp8 value scale
@@ -1871,6 +1896,7 @@ void tile64_kernel(const PartialParams p) {
   };
   // the weights against the running maximum, their sum, and their bf16 form to LDS
   auto put_p = [&]() {
+    if (!act) return;
     f32x4_t e;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1891,8 +1917,12 @@ void tile64_kernel(const PartialParams p) {
   // scores, log2 units: the products are rounded before a maximum is taken off
   // them (opaque to contraction): under a scale of 2^64 a fused
   // multiply-subtract would leave the rounding error of the maximum itself.
-  float mx = 0.f;
+  float mx = -INFINITY;
   auto soft = [&](int part, int stage) {
+    if (!act) {
+      if (part == 1) flags[8 * lane + wave] = 0;
+      return;
+    }
     if (part == 0) {
       x_stage = stage;
       // (fp8, see fp8_factors: scores are main * (latent part + ratio * RoPE
@@ -1935,7 +1965,7 @@ void tile64_kernel(const PartialParams p) {
   using VRing = typename std::conditional<FP8, i32x2_t, bf16x8_t>::type;
   VRing vr[4];
   bf16x8_t vc[4];     // fp8: the converted fragments
-  bf16x8_t pb[2][2];  // weights [16 tokens][row half]
+  bf16x8_t pb[2][NK];  // weights [16 tokens][row half]
   uint32_t v_st = 0;
   auto vload = [&](int f) {
     LDS uint8_t* const a = lds_at(v_off[f] + v_st);
@@ -1954,13 +1984,14 @@ void tile64_kernel(const PartialParams p) {
   };
   auto pload = [&](int i, int kk) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < NK; ++k)
       pb[kk][k] = lds_b128(pbuf + ((i & 1) << 12) + ((2 * kk + k) << 10) + (lane << 4));
   };
   auto pv_one = [&](int f, int k, bool pre) {
     bf16x8_t v;
     if constexpr (FP8) v = vc[f];
     else v = vr[f];
+    if (k >= NK) return;
     __builtin_amdgcn_sched_barrier(0);
     if (pre) pv<true>(O[f & 1][k], v, pb[f >> 1][k]);
     else pv<false>(O[f & 1][k], v, pb[f >> 1][k]);
@@ -1995,41 +2026,48 @@ void tile64_kernel(const PartialParams p) {
       const u32x4_t w = __builtin_bit_cast(u32x4_t, kr[j % (kAhead + 1)]);
       return e4m3x8_bf16(w[2 * e], w[2 * e + 1]);
     };
+    if (act) {
 #pragma unroll
-    for (int j = 0; j < kAhead; ++j) key_read(j);
+      for (int j = 0; j < kAhead; ++j) key_read(j);
+    }
     u32x2_t ask{};
     if constexpr (kMid) ask = *(LDS const u32x2_t*)(flags + 8 * lane);
     const bool ld = ih < n;
     if constexpr (kMid) pv_one(3, 0, true);
     if (ld) aim(ih);
     if constexpr (kMid) pv_one(3, 1, false);
-    if constexpr (FP8) {
-      ka[0] = half_of(0, 0);
-      ka[1] = half_of(0, 1);
-      pin(ka[0]);
-      pin(ka[1]);
-    }
-    auto steps = [&](auto with_loads) {
+    auto steps = [&](auto with_loads, auto with_products) {
       constexpr bool kLd = decltype(with_loads)::value;
+      constexpr bool kMul = decltype(with_products)::value;
+      // (without products of its own, a wave waits here until O may be read)
+      if constexpr (!kMul) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+      if constexpr (FP8 && kMul) {
+        ka[0] = half_of(0, 0);
+        ka[1] = half_of(0, 1);
+        pin(ka[0]);
+        pin(ka[1]);
+      }
 #pragma unroll
       for (int step = 0; step < 18; ++step) {
-        bf16x8_t a;
-        if constexpr (FP8) a = ka[step & 3];
-        else a = kr[step % (kAhead + 1)];
-        f32x4_t& acc = kSplitScales && step < 2 ? pacc : sacc;
-        __builtin_amdgcn_sched_barrier(0);
-        if (step == 0 || (kSplitScales && step == 2)) stq<true, false, FP8>(acc, a, qb[step]);
-        else if (step == 17) stq<false, true, false>(acc, a, qb[step]);
-        else stq<false, false, false>(acc, a, qb[step]);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (FP8) {
-          if ((step & 1) == 0 && step / 2 + kAhead < kReads) key_read(step / 2 + kAhead);
-          if (step + 2 < 18) {
-            ka[(step + 2) & 3] = half_of((step + 2) / 2, step & 1);
-            pin(ka[(step + 2) & 3]);
+        if constexpr (kMul) {
+          bf16x8_t a;
+          if constexpr (FP8) a = ka[step & 3];
+          else a = kr[step % (kAhead + 1)];
+          f32x4_t& acc = kSplitScales && step < 2 ? pacc : sacc;
+          __builtin_amdgcn_sched_barrier(0);
+          if (step == 0 || (kSplitScales && step == 2)) stq<true, false, FP8>(acc, a, qb[step]);
+          else if (step == 17) stq<false, true, false>(acc, a, qb[step]);
+          else stq<false, false, false>(acc, a, qb[step]);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (FP8) {
+            if ((step & 1) == 0 && step / 2 + kAhead < kReads) key_read(step / 2 + kAhead);
+            if (step + 2 < 18) {
+              ka[(step + 2) & 3] = half_of((step + 2) / 2, step & 1);
+              pin(ka[(step + 2) & 3]);
+            }
+          } else {
+            if (step + kAhead < kReads) key_read(step + kAhead);
           }
-        } else {
-          if (step + kAhead < kReads) key_read(step + kAhead);
         }
         if (kLd && step % 3 == 1 && step / 3 < L::kLoads) is.load(p, step / 3, lane);
         // what the softmax and the value products of this step need
@@ -2049,8 +2087,16 @@ void tile64_kernel(const PartialParams p) {
         }
       }
     };
-    if (ld) steps(std::true_type{});
-    else steps(std::false_type{});
+    if constexpr (NK == 2) {
+      if (ld) steps(std::true_type{}, std::true_type{});
+      else steps(std::false_type{}, std::true_type{});
+    } else if (act) {
+      if (ld) steps(std::true_type{}, std::true_type{});
+      else steps(std::false_type{}, std::true_type{});
+    } else {
+      if (ld) steps(std::true_type{}, std::false_type{});
+      else steps(std::false_type{}, std::false_type{});
+    }
     return ask;
   };
   // Lazy rescale: the maxima move only when some row's grows by more than the
@@ -2059,10 +2105,12 @@ void tile64_kernel(const PartialParams p) {
   // The first stage always comes here, its row maxima exchanged already.
   auto put_max = [&]() {
     const float m = xor_max(mx);
-    if (g == 0) xmax[(16 * rq + n16) * 2 + th] = m;
+    if (act && g == 0) xmax[(16 * rq + n16) * 2 + th] = m;
   };
   auto settle = [&](int i, u32x2_t ask) {
-    float alpha[2] = {1.f, 1.f};
+    float alpha[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) alpha[k] = 1.f;
     int any = 0;
     if (i == 0 || __ballot((ask[0] | ask[1]) != 0) != 0) {
       if (i != 0) {
@@ -2080,15 +2128,21 @@ void tile64_kernel(const PartialParams p) {
         return alpha;
       };
       const f32x2_t b = *(LDS const f32x2_t*)(xmax + 2 * (16 * rq + n16));
-      const f32x2_t b0 = *(LDS const f32x2_t*)(xmax + 2 * n32), b1 = *(LDS const f32x2_t*)(xmax + 2 * (32 + n32));
+      f32x2_t ball[NK];
+#pragma unroll
+      for (int k = 0; k < NK; ++k) ball[k] = *(LDS const f32x2_t*)(xmax + 2 * (32 * k + n32));
       __builtin_amdgcn_sched_barrier(0);  // one trip to LDS for all
       const float own = raise(b, m_run);
       l_run *= own;
       l_norm *= own;
       put_p();
-      alpha[0] = raise(b0, m_all[0]);
-      alpha[1] = raise(b1, m_all[1]);
-      any = __ballot(alpha[0] != 1.f || alpha[1] != 1.f) != 0;
+      bool moved = false;
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        alpha[k] = raise(ball[k], m_all[k]);
+        moved |= alpha[k] != 1.f;
+      }
+      any = __ballot(moved) != 0;
       lds_barrier();
       pload(i, 0);
     }
@@ -2111,6 +2165,9 @@ void tile64_kernel(const PartialParams p) {
       if (f == 0) pload(i, 1);
       if (f + 2 < 4) vconv(f + 2);
       pv_one(f, 1, false);
+      // (with one product a fragment, what the compiler moves aside of O to make
+      // room for the tokens' scales would come too soon after it)
+      if constexpr (NK == 1 && FP8 && TOK && kSoft) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2");
       if (kSoft) soft(f, i + 1);
     }
   };
@@ -2124,12 +2181,13 @@ void tile64_kernel(const PartialParams p) {
     // (nothing is left over before the first step: products of zeros)
     vr[3] = VRing{};
     vc[3] = bf16x8_t{};
-    pb[1][0] = bf16x8_t{};
-    pb[1][1] = bf16x8_t{};
     pin(vr[3]);
     pin(vc[3]);
-    pin(pb[1][0]);
-    pin(pb[1][1]);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      pb[1][k] = bf16x8_t{};
+      pin(pb[1][k]);
+    }
     for (int i = 0; i + 1 < n; ++i) {
       meet(i);
       v_st = (uint32_t)((i % L::kNum) * L::kStage);
@@ -2167,7 +2225,7 @@ void tile64_kernel(const PartialParams p) {
     const float l = xor_sum(l_run);
     const float ln = xor_sum(l_norm);
     const float mt = xor_max(m_true);
-    if (g == 0) {
+    if (act && g == 0) {
       xnorm[(16 * rq + n16) * 2 + th] = ln;
       xsum[(16 * rq + n16) * 2 + th] = l;
       xtrue[(16 * rq + n16) * 2 + th] = mt;
@@ -2175,7 +2233,7 @@ void tile64_kernel(const PartialParams p) {
   }
   if (half) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NK; ++k) {
       float am = 0.f;
 #pragma unroll
       for (int d = 0; d < 2; ++d) {
@@ -2189,12 +2247,12 @@ void tile64_kernel(const PartialParams p) {
   }
   lds_barrier();
   // the rows' statistics, both halves before the first store (their LDS trips overlap)
-  float mult[2];
+  float mult[NK];
   {
-    f32x2_t ls[2], lw[2];
-    f32x4_t am[2], an[2];
+    f32x2_t ls[NK], lw[NK];
+    f32x4_t am[NK], an[NK];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NK; ++k) {
       const int rl = 32 * k + n32;
       ls[k] = *(LDS const f32x2_t*)(xsum + 2 * rl);
       lw[k] = *(LDS const f32x2_t*)(xnorm + 2 * rl);
@@ -2202,7 +2260,7 @@ void tile64_kernel(const PartialParams p) {
       an[k] = *(LDS const f32x4_t*)(xamax + 8 * rl + 4);
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NK; ++k) {
       const int rl = 32 * k + n32, row = row_wg0 + rl;
       const float l_tot = ls[k][0] + ls[k][1];
       mult[k] = l_tot > 0.f ? recip(lw[k][0] + lw[k][1]) : 0.f;
@@ -2240,7 +2298,7 @@ void tile64_kernel(const PartialParams p) {
   // store instruction 64-byte runs of 16 rows: row 16 j + (lane & 15) of half k.
   const int q = lane >> 4;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < NK; ++k) {
     // the element offsets of this lane's two rows
     int64_t off[2];
     bool ok[2];
@@ -2318,10 +2376,15 @@ void tile64_kernel(const PartialParams p) {
 
 template <int KV, int SEL = kSelShared>
 static void launch_kv(const PartialParams& p, int grid, int row_groups, hipStream_t s) {
-  if (row_groups == 2)
+  if (row_groups == 2) {
     hipLaunchKernelGGL((partial_kernel<KV, SEL>), dim3(grid), dim3(256), 0, s, p);
+    return;
+  }
+  // jobs of 32 rows at most: half a tile
+  if (p.rows <= 32)
+    hipLaunchKernelGGL((tile64_kernel<KV, SEL, 1>), dim3(grid), dim3(512), 0, s, p);
   else
-    hipLaunchKernelGGL((tile64_kernel<KV, SEL>), dim3(grid), dim3(512), 0, s, p);
+    hipLaunchKernelGGL((tile64_kernel<KV, SEL, 2>), dim3(grid), dim3(512), 0, s, p);
 }
 
 hipError_t launch_partial(const PartialParams& p, int R, int kv, int row_groups, int sel_kind,

@@ -92,3 +92,21 @@ def test_strided_queries_and_rising_maxima(wire):
         if wire:
             lse = lse[..., 0] + np.log(lse[..., 1])
         G.assert_parity(out.double().cpu().numpy(), lse, ref_o, ref_l, f"wire={wire} splits={ns}")
+
+
+@pytest.mark.parametrize("kind", ["blocks", "tokens", "per_row"])
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp8split"])
+@pytest.mark.parametrize("mq,h", [(16, 1), (2, 16), (3, 11)])
+def test_half_tiles(mq, h, kv, kind):
+    # 16, 32 and 33 rows: the last takes both row halves; from one stage to
+    # beyond the ring, blocks of growing magnitude so that maxima rise
+    k = {"blocks": 9, "tokens": 289, "per_row": 5}[kind]
+    w = W.random_case(1010 + 7 * mq + h, R=2, Mq=mq, H=h, P=16, NB=11, K=k, tokens=kind == "tokens",
+                      per_row=kind == "per_row")
+    for j in range(11):
+        b = w.table[0, j]
+        w.ckv[b] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(w.ckv[b]) * np.float32(0.25 * 1.5 ** j))
+    if kv != "bf16":
+        w = w.to_fp8(kv == "fp8")
+    for ns in (1, 3):
+        _check(w, f"half tile {mq}x{h} {kv} {kind} splits={ns}", n_splits=ns)
