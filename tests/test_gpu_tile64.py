@@ -110,3 +110,24 @@ def test_half_tiles(mq, h, kv, kind):
         w = w.to_fp8(kv == "fp8")
     for ns in (1, 3):
         _check(w, f"half tile {mq}x{h} {kv} {kind} splits={ns}", n_splits=ns)
+
+
+@pytest.mark.parametrize("shared_q", [False, True])
+def test_per_row_lists_beyond_the_scratch(shared_q):
+    # 64 query rows x 16 slots a tile: two splits, whose rows exceed the
+    # allocation-free entry's scratch for all jobs together
+    R, Mq, K, NB = 600, 64, 16, 24
+    print(f"case: per-row beyond scratch shared_q={shared_q}", flush=True)
+    w = W.random_case(1100, R=R, Mq=Mq, H=1, P=40, NB=NB, K=K, per_row=True)
+    t = G.upload(w)
+    n_q = R // 2 if shared_q else R
+    args = (t["q_lat"][:n_q], t["q_pe"][:n_q], t["ckv"], t["kpe"], t["table"], t["sel"], w.scale)
+    for rt in (0, 64):
+        out, lse = mla.sparse_partial_attn(*args, row_tile=rt, no_alloc=True)
+        ref_o, ref_l = mla.sparse_partial_attn(*args, row_tile=128, n_splits=1)
+        torch.cuda.synchronize()
+        # the split rows' fp16 rounding and the weights' to bf16, in both plans
+        err = (out - ref_o).abs().amax(-1) / ref_o.abs().amax(-1).clamp_min(1e-30)
+        assert float(err.max()) <= 2 * (2 ** -8 + 2 ** -11), float(err.max())
+        same = (lse == ref_l) | ((lse - ref_l).abs() <= 1e-4)
+        assert bool(same.all())
