@@ -159,6 +159,17 @@ constexpr int kPerRowMaxRows = 64;                  // query rows per row tile (
 // (elsewhere kMaxSlotsPerSplit)
 constexpr int kPerRowListShort = kMaxSlotsPerSplit / 2;
 
+// 64-row tiles: the waves' requests to raise a stage's maxima, a byte per wave
+// and lane, in two places by the parity of the stage.  Every wave reads those
+// of stage i in step i and writes its own for stage i + 1 later in the same
+// step, and no barrier lies between one wave's read and another's write: in one
+// place a wave that is late after the step's barrier could take a request of
+// the next stage for one of this, enter the exchange of the maxima alone, and
+// meet the others at the wrong barrier.  Place i & 1 is written again in step
+// i + 1, after a barrier that the late wave has to reach as well.
+constexpr int kAskBytes = 512;
+__host__ __device__ constexpr int ask_place(int stage) { return (stage & 1) * kAskBytes; }
+
 // Selection kinds: one block selection per job, one per query row, or one
 // token selection per job (bf16 caches only for the last two).
 constexpr int kSelShared = 0;

@@ -1456,9 +1456,9 @@ struct Tile {
   static constexpr int kWaveCnt = kMasks + (PR ? kCap * 8 : 0);
   static constexpr int kP = FP8 && PR ? kRing : kWaveCnt + 256;
   static constexpr int kX = kP + 8192;       // row maxima [64 rows][2 token groups]
-  static constexpr int kFlags = kX + 512;    // a byte per wave and lane
-  static constexpr int kTotal = FP8 && PR ? kWaveCnt + 32 : kFlags + 512;
-  static_assert(kRing <= kList && kFlags + 512 <= (FP8 && PR ? kList : kTotal), "areas apart");
+  static constexpr int kAsk = kX + 512;      // requests to raise a maximum, see ask_place
+  static constexpr int kTotal = FP8 && PR ? kWaveCnt + 32 : kAsk + 2 * kAskBytes;
+  static_assert(kRing <= kList && kAsk + 2 * kAskBytes <= (FP8 && PR ? kList : kTotal), "areas apart");
 };
 static_assert(Tile<false, true>::kTotal <= 160 * 1024 && Tile<true, true>::kTotal <= 160 * 1024 &&
                   Tile<true, false>::kTotal <= 160 * 1024 && Tile<false, false>::kTotal <= 160 * 1024,
@@ -1713,7 +1713,8 @@ void tile64_kernel(const PartialParams p) {
   LDS uint64_t* masks = (LDS uint64_t*)(smem + L::kMasks);
   LDS uint8_t* const pbuf = smem + L::kP;
   LDS float* const xmax = (LDS float*)(smem + L::kX);
-  LDS uint8_t* const flags = smem + L::kFlags;
+  // the requests of a stage: byte 8 lane + wave
+  auto asks = [&](int stage) { return smem + L::kAsk + ask_place(stage); };
   const int row_wg0 = rt * 64;
   const int i0 = div_by(row_wg0, p.by_H);
   const int n_i = PR ? div_by(min(row_wg0 + 64, p.rows) - 1, p.by_H) - i0 + 1 : 1;
@@ -1920,7 +1921,7 @@ void tile64_kernel(const PartialParams p) {
   float mx = -INFINITY;
   auto soft = [&](int part, int stage) {
     if (!act) {
-      if (part == 1) flags[8 * lane + wave] = 0;
+      if (part == 1) asks(stage)[8 * lane + wave] = 0;
       return;
     }
     if (part == 0) {
@@ -1953,7 +1954,7 @@ void tile64_kernel(const PartialParams p) {
       if (PR && !on) mx = -INFINITY;
       m_true = fmaxf(m_true, mx);
     } else if (part == 1) {
-      flags[8 * lane + wave] = mx > m_run + kTau;
+      asks(stage)[8 * lane + wave] = mx > m_run + kTau;
     } else {
       put_p();
     }
@@ -2031,7 +2032,7 @@ void tile64_kernel(const PartialParams p) {
       for (int j = 0; j < kAhead; ++j) key_read(j);
     }
     u32x2_t ask{};
-    if constexpr (kMid) ask = *(LDS const u32x2_t*)(flags + 8 * lane);
+    if constexpr (kMid) ask = *(LDS const u32x2_t*)(asks(i) + 8 * lane);
     const bool ld = ih < n;
     if constexpr (kMid) pv_one(3, 0, true);
     if (ld) aim(ih);
@@ -2197,7 +2198,7 @@ void tile64_kernel(const PartialParams p) {
     }
     const int i = n - 1;
     lds_barrier();
-    const u32x2_t ask = *(LDS const u32x2_t*)(flags + 8 * lane);
+    const u32x2_t ask = *(LDS const u32x2_t*)(asks(i) + 8 * lane);
     v_st = (uint32_t)((i % L::kNum) * L::kStage);
     if (n > 1) {
       pv_one(3, 0, true);
