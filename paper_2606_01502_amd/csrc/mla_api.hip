@@ -14,7 +14,9 @@
 #include <vector>
 
 #include "../../include/mla_sparse.h"
-#include "mla_kernels.h"
+#include "mla_plan.h"
+
+static_assert(mla::kPlanScratch == MLA_NOALLOC_SCRATCH_BYTES, "plans fit the allocation-free entry");
 
 namespace {
 
@@ -306,156 +308,20 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     const int64_t rows = Mq * H;
     if (R == 0 || rows == 0) return MLA_OK;
 
-    // ---- plan: row tiles of 128 or 64 rows (4 waves of 32 rows or 8 that share
-    // them); split-K over slot ranges so that the grid covers the chip
-    // slots in 64-token blocks (a token selection's slots fill K / 64 blocks)
-    const int64_t Kb = tokens ? (K + 63) / 64 : K;
-    // per-row selections: the query rows a row tile spans (one mask bit each)
-    auto tile_query_rows = [&](int rg) {
-      const int64_t rw = 64 * rg;
-      int64_t most = 0;
-      for (int64_t r0 = 0; r0 < rows; r0 += rw) {
-        const int64_t last = std::min<int64_t>(r0 + rw, rows) - 1;
-        most = std::max<int64_t>(most, last / H - r0 / H + 1);
-      }
-      return most;
-    };
-    // the row groups (of 64 rows) of a tile: the caller's; 1 where a job has no
-    // more rows; 2 for per-row selections whose splits are long (8 blocks and
-    // more), where a tile of twice the rows shares more loads; 0: the cheaper,
-    // below
-    int row_groups = 0;
-    if (opts && opts->row_tile) {
-      row_groups = opts->row_tile / 64;
-    } else if (rows <= 64) {
-      row_groups = 1;
-    } else if (per_row) {
-      const int64_t units2 = R * ((rows + 127) / 128);
-      const int64_t s2 = std::min<int64_t>((device_cus() + units2 - 1) / units2,
-                                           std::max<int64_t>(Kb / 2, 1));
-      row_groups = Kb < 8 * s2 ? 1 : 2;
-    }
-    int64_t tile_qrows = 1;
-    if (per_row) {
-      if (row_groups == 2 && tile_query_rows(2) > mla::kPerRowMaxRows) {
-        if (opts && opts->row_tile == 128)
-          return fail(MLA_ERR_UNSUPPORTED, "per-row selections: too many query rows per 128-row tile");
-        row_groups = 1;
-      }
-      tile_qrows = tile_query_rows(row_groups);
-      if (tile_qrows > mla::kPerRowMaxRows)
-        return fail(MLA_ERR_UNSUPPORTED, "per-row selections: too many query rows per tile");
-      if (NB * tile_qrows * 2 > mla::kPerRowCounterBytes)
-        return fail(MLA_ERR_UNSUPPORTED, "per-row selections: NB x query rows per tile too large");
-    }
-    // split rows in the workspace, then their scales (fp16 rows only), then
-    // their lse values and maxima.  fp16 rows halve the workspace round trip,
-    // which pays from about a megabyte of split rows on; tiny workspaces keep
-    // fp32 rows, whose epilogue is a little shorter
-    auto ws_half = [&](int64_t S) {
-      return (size_t)R * S * rows * MLA_DLAT * sizeof(float) >= (size_t)mla::kWsHalfMinBytes;
-    };
-    auto ws_rows_bytes = [&](int64_t S) {
-      return (size_t)R * S * rows * MLA_DLAT * (ws_half(S) ? sizeof(uint16_t) : sizeof(float));
-    };
-    auto ws_size = [&](int64_t S) { return ws_rows_bytes(S) + 3 * (size_t)R * S * rows * sizeof(float); };
-    struct Plan {
-      int row_groups;
-      int64_t row_tiles, S, sps;
-      bool by_id;
-      double us;
-    };
-    auto row_tiles_of = [&](int rg) { return (rows + 64 * rg - 1) / (64 * rg); };
-    // entries one split's list holds (per-row selections with an fp8 cache or
-    // 64-row tiles: a shorter one, see the kernel's LDS layout)
-    auto list_cap_of = [&](int rg) -> int64_t {
-      return per_row && (fp8 || rg == 1) ? mla::kPerRowListShort : mla::kMaxSlotsPerSplit;
-    };
-    // per-row selections whose tile slots all fit one list split by logical
-    // block: every split then scans all slots and the rows that chose a block
-    // in different slots still share its load
-    auto by_id_of = [&](int rg) { return per_row && tile_qrows > 1 && K * tile_qrows <= list_cap_of(rg); };
-    // the most blocks a tile can visit
-    auto blocks_of = [&](int rg) { return by_id_of(rg) ? std::min<int64_t>(NB, K * tile_qrows) : Kb; };
-    // the plan of about S splits with tiles of rg row groups, and its time
-    auto plan_of = [&](int rg, int64_t S) {
-      Plan q{rg, row_tiles_of(rg), S, K, by_id_of(rg), 0.0};
-      const int64_t list_cap = list_cap_of(rg);
-      // a split's block list holds at most list_cap entries: its slots, or for
-      // per-row selections its slots of every query row of the tile
-      if (tokens) {
-        // whole virtual blocks per split, at most one list of tokens
-        S = std::max<int64_t>(S, (K + mla::kMaxSlotsPerSplit - 1) / mla::kMaxSlotsPerSplit);
-        q.sps = std::max<int64_t>(64, ((K + S - 1) / S + 63) / 64 * 64);
-        q.sps = std::min<int64_t>(q.sps, mla::kMaxSlotsPerSplit);
-        q.S = std::max<int64_t>(1, (K + q.sps - 1) / q.sps);
-      } else if (!q.by_id) {
-        S = std::max<int64_t>(S, (K * tile_qrows + list_cap - 1) / list_cap);
-        q.sps = std::max<int64_t>(1, (K + S - 1) / S);
-        if (per_row) q.sps = std::min<int64_t>(q.sps, std::max<int64_t>(1, list_cap / tile_qrows));
-        q.S = std::max<int64_t>(1, (K + q.sps - 1) / q.sps);
-      }
-      // What a call takes, microseconds.  A workgroup fills its CU, so that a
-      // grid goes in waves of one a CU; a work item takes a fixed part (its
-      // prologue, query rows and epilogue) and its blocks' time (more where two
-      // 64-row tiles load a block each); splits add the combine, by the rows it
-      // reads.  Fitted to 1300 timed calls of 3..300 jobs of 16, 64 and 128 rows
-      // x 8..600 blocks with 1..90 splits (8 % rms) and 600 of tokens.
-      const double blocks = q.by_id ? (double)((blocks_of(rg) + q.S - 1) / q.S)
-                          : tokens ? (double)((q.sps + 63) / 64)
-                          : per_row ? (double)std::min<int64_t>(std::max<int64_t>(NB, 1), q.sps * tile_qrows)
-                          : (double)q.sps;
-      const double fixed_us = rg == 1 ? 6.4 : fp8 ? 11.0 : 10.5;
-      const double block_us = rg == 1 ? (tokens ? (fp8 ? 2.9 : 4.2) : rows <= 64 ? 2.15 : fp8 ? 2.3 : 2.4)
-                                      : (tokens ? (fp8 ? 5.0 : 4.1) : fp8 ? 4.0 : 3.6);
-      const double waves = std::ceil((double)R * q.row_tiles * q.S / device_cus());
-      q.us = waves * (fixed_us + blocks * block_us);
-      if (q.S > 1) q.us += 1.5 + 0.3e-3 * (double)R * q.S * rows;
-      return q;
-    };
-    Plan plan{};
-    if (opts && opts->n_splits > 0) {
-      for (int rg = 2; rg >= 1; --rg) {
-        if (row_groups && rg != row_groups) continue;
-        const Plan q = plan_of(rg, std::min<int64_t>(opts->n_splits, std::max<int64_t>(by_id_of(rg) ? NB : K, 1)));
-        if (!plan.row_groups || q.us < plan.us) plan = q;
-      }
-    } else {
-      // One split, or as many as one, two or three waves of workgroups hold; at
-      // least two blocks a split (one block costs less than its split's fixed
-      // part).  A grid just past a whole number of waves costs a wave more: 20
-      // jobs of 128 rows x 200 blocks take 122 us in 13 splits (260 workgroups)
-      // and 85 in 12, 40 x 600 blocks 622 and 420 (fp8 708 and 446), 24 of 2048
-      // tokens 67 and 39.  Several waves of shorter splits where one wave leaves
-      // CUs idle, and are taken where they promise 7 % and more: 300 jobs of 64
-      // rows x 64 blocks 305 us in one split, 266 in three.  A fourth wave gains
-      // nothing over the sizes above.  The split rows of a plan stay within the
-      // allocation-free entry's scratch (64 MiB), for every entry.
-      // Two splits of at most two blocks save at most two blocks' time and add
-      // the combine's launch: one split does better (4 blocks of one 16-row
-      // job: 12.4 us in one split against 14.9 in two).
-      for (int rg = 1; rg <= 2; ++rg) {
-        if (row_groups && rg != row_groups) continue;
-        const int64_t units = std::max<int64_t>(R * row_tiles_of(rg), 1);
-        const int64_t most = std::max<int64_t>(blocks_of(rg) / 2, 1);
-        for (int waves = 0; waves <= 3; ++waves) {
-          const int64_t S = std::max<int64_t>(1, std::min<int64_t>(waves * device_cus() / units, most));
-          if (S == 2 && !by_id_of(rg) && Kb <= 5) continue;
-          const Plan q = plan_of(rg, S);
-          if (plan.row_groups && q.S > 1 && ws_size(q.S) > (size_t)MLA_NOALLOC_SCRATCH_BYTES) continue;
-          if (!plan.row_groups || q.us < plan.us * (waves > 1 ? 0.93 : 1.0)) plan = q;
-        }
-      }
-    }
-    row_groups = plan.row_groups;
-    const int64_t row_tiles = plan.row_tiles, S = plan.S, sps = plan.sps;
+    // row tiles and split-K
+    const mla::Planner planner({R, Mq, H, NB, K, tokens, per_row, fp8, opts ? opts->n_splits : 0,
+                                opts ? opts->row_tile : 0, device_cus()});
+    if (planner.refused) return fail(MLA_ERR_UNSUPPORTED, planner.refused);
+    const mla::Plan plan = planner.choose();
+    const int row_groups = plan.row_groups;
+    const int64_t row_tiles = plan.row_tiles, S = plan.S, sps = plan.sps, tile_qrows = planner.tile_qrows;
     const bool by_id = plan.by_id;
     // Per-row selections of a bf16 cache in 64-row tiles whose slots fit a
     // 128-row tile's list but not their own shorter one need two splits where
     // one might do.  Where those exceed the allocation-free entry's scratch, the
     // call goes job range by job range (one after the other on the stream).
     if (no_alloc && per_row && !fp8 && row_groups == 1 && K * tile_qrows <= mla::kMaxSlotsPerSplit &&
-        !(opts && opts->n_splits > 1) && R > 1 && S > 1 && ws_size(S) > (size_t)MLA_NOALLOC_SCRATCH_BYTES) {
+        !(opts && opts->n_splits > 1) && R > 1 && S > 1 && planner.ws_size(S) > (size_t)MLA_NOALLOC_SCRATCH_BYTES) {
       const int64_t fit = std::max<int64_t>(
           1, MLA_NOALLOC_SCRATCH_BYTES / (S * rows * (int64_t)(MLA_DLAT * sizeof(uint16_t) + 3 * sizeof(float))));
       // as small jobs' rows may be kept in fp32: half as many
@@ -531,9 +397,9 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     std::unique_lock<std::mutex> ws_lock;  // held until the combine is queued
     if (S > 1) {
       const size_t n_part_rows = (size_t)R * S * rows;
-      p.ws_f16 = ws_half(S);
-      const size_t o_bytes = ws_rows_bytes(S);
-      const size_t ws_bytes = ws_size(S);
+      p.ws_f16 = planner.ws_half(S);
+      const size_t o_bytes = planner.ws_rows_bytes(S);
+      const size_t ws_bytes = planner.ws_size(S);
       void* ws = nullptr;
       if (no_alloc) {
         if (ws_bytes > (size_t)MLA_NOALLOC_SCRATCH_BYTES)

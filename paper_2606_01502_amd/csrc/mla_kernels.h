@@ -15,7 +15,7 @@ constexpr int kMaxSlotsPerSplit = 1024;   // selected-slot range one workgroup h
 constexpr int kMaxParts = 64;
 // split-K workspaces of at least this many fp32 row bytes store scaled fp16
 // rows (below it, as for a handful of rows, the shorter fp32 epilogue pays)
-constexpr int64_t kWsHalfMinBytes = 1ll << 20;
+constexpr uint64_t kWsHalfMinBytes = 1ull << 20;
 
 // Division of 0 <= n < 2^31 by a divisor d >= 1 that the host knows: n m >> s
 // with s = 31 + ceil(log2 d), m = floor(2^s / d) + 1.  m d = 2^s + e with 0 < e

@@ -1,0 +1,185 @@
+// The plan of a partial call: row tile, splits and what they keep in the
+// split-K workspace.  Host arithmetic only.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "mla_kernels.h"
+
+namespace mla {
+
+// What the plan is made from: jobs, query rows and heads of a job, logical
+// blocks and slots of a selection, its kind, the caller's options (0: the
+// library's choice) and the compute units of the device.
+struct PlanArgs {
+  int64_t R, Mq, H, NB, K;
+  bool tokens, per_row, fp8;
+  int32_t n_splits, row_tile;
+  int64_t cus;
+};
+
+struct Plan {
+  int row_groups;          // of 64 rows a tile: 1 or 2
+  int64_t row_tiles;       // tiles of a job
+  int64_t S, sps;          // splits of a tile's slots, slots of a split
+  bool by_id;              // splits by logical block instead of slot range
+  double us;               // what the call should take
+};
+
+// Bytes of split rows that a plan stays within where any plan does: what the
+// allocation-free entry's scratch array holds.
+constexpr uint64_t kPlanScratch = 64ull << 20;
+
+struct Planner {
+  PlanArgs a;
+  int64_t rows, Kb;        // of a job; slots in 64-token blocks
+  int64_t tile_qrows = 1;  // per-row selections: query rows a tile spans (one mask bit each)
+  int row_groups = 0;      // of every plan, or 0: either
+  const char* refused = nullptr;
+
+  explicit Planner(const PlanArgs& args) : a(args), rows(a.Mq * a.H) {
+    Kb = a.tokens ? (a.K + 63) / 64 : a.K;  // a token selection's slots fill K / 64 blocks
+    // the row groups of a tile: the caller's; 1 where a job has no more rows; 2
+    // for per-row selections whose splits are long (8 blocks and more), where a
+    // tile of twice the rows shares more loads; 0: the cheaper
+    if (a.row_tile) {
+      row_groups = a.row_tile / 64;
+    } else if (rows <= 64) {
+      row_groups = 1;
+    } else if (a.per_row) {
+      const int64_t units2 = a.R * row_tiles_of(2);
+      const int64_t s2 = std::min<int64_t>((a.cus + units2 - 1) / units2, std::max<int64_t>(Kb / 2, 1));
+      row_groups = Kb < 8 * s2 ? 1 : 2;
+    }
+    if (!a.per_row) return;
+    if (row_groups == 2 && tile_query_rows(2) > kPerRowMaxRows) {
+      if (a.row_tile == 128) {
+        refused = "per-row selections: too many query rows per 128-row tile";
+        return;
+      }
+      row_groups = 1;
+    }
+    tile_qrows = tile_query_rows(row_groups);
+    if (tile_qrows > kPerRowMaxRows) refused = "per-row selections: too many query rows per tile";
+    else if (a.NB * tile_qrows * 2 > kPerRowCounterBytes)
+      refused = "per-row selections: NB x query rows per tile too large";
+  }
+
+  int64_t row_tiles_of(int rg) const { return (rows + 64 * rg - 1) / (64 * rg); }
+
+  int64_t tile_query_rows(int rg) const {
+    const int64_t rw = 64 * rg;
+    int64_t most = 0;
+    for (int64_t r0 = 0; r0 < rows; r0 += rw) {
+      const int64_t last = std::min<int64_t>(r0 + rw, rows) - 1;
+      most = std::max<int64_t>(most, last / a.H - r0 / a.H + 1);
+    }
+    return most;
+  }
+
+  // Split rows in the workspace, then their scales (fp16 rows only), then their
+  // lse values and maxima.  fp16 rows halve the workspace round trip, which pays
+  // from about a megabyte of split rows on; tiny workspaces keep fp32 rows,
+  // whose epilogue is a little shorter.
+  uint64_t split_rows(int64_t S) const { return (uint64_t)a.R * S * rows; }
+  bool ws_half(int64_t S) const { return split_rows(S) * kDLat * 4 >= kWsHalfMinBytes; }
+  uint64_t ws_rows_bytes(int64_t S) const { return split_rows(S) * kDLat * (ws_half(S) ? 2 : 4); }
+  uint64_t ws_size(int64_t S) const { return ws_rows_bytes(S) + 3 * split_rows(S) * 4; }
+  bool fits(const Plan& q) const { return q.S <= 1 || ws_size(q.S) <= kPlanScratch; }
+
+  // entries one split's list holds (per-row selections with an fp8 cache or
+  // 64-row tiles: a shorter one, see the kernel's LDS layout)
+  int64_t list_cap_of(int rg) const {
+    return a.per_row && (a.fp8 || rg == 1) ? kPerRowListShort : kMaxSlotsPerSplit;
+  }
+  // per-row selections whose tile slots all fit one list split by logical
+  // block: every split then scans all slots and the rows that chose a block
+  // in different slots still share its load
+  bool by_id_of(int rg) const { return a.per_row && tile_qrows > 1 && a.K * tile_qrows <= list_cap_of(rg); }
+  // the most blocks a tile can visit
+  int64_t blocks_of(int rg) const { return by_id_of(rg) ? std::min<int64_t>(a.NB, a.K * tile_qrows) : Kb; }
+
+  // the plan of about S splits with tiles of rg row groups, and its time
+  Plan plan_of(int rg, int64_t S) const {
+    Plan q{rg, row_tiles_of(rg), S, a.K, by_id_of(rg), 0.0};
+    const int64_t list_cap = list_cap_of(rg);
+    // a split's block list holds at most list_cap entries: its slots, or for
+    // per-row selections its slots of every query row of the tile
+    if (a.tokens) {
+      // whole virtual blocks per split, at most one list of tokens
+      S = std::max<int64_t>(S, (a.K + kMaxSlotsPerSplit - 1) / kMaxSlotsPerSplit);
+      q.sps = std::max<int64_t>(64, ((a.K + S - 1) / S + 63) / 64 * 64);
+      q.sps = std::min<int64_t>(q.sps, kMaxSlotsPerSplit);
+      q.S = std::max<int64_t>(1, (a.K + q.sps - 1) / q.sps);
+    } else if (!q.by_id) {
+      S = std::max<int64_t>(S, (a.K * tile_qrows + list_cap - 1) / list_cap);
+      q.sps = std::max<int64_t>(1, (a.K + S - 1) / S);
+      if (a.per_row) q.sps = std::min<int64_t>(q.sps, std::max<int64_t>(1, list_cap / tile_qrows));
+      q.S = std::max<int64_t>(1, (a.K + q.sps - 1) / q.sps);
+    }
+    // What a call takes, microseconds.  A workgroup fills its CU, so that a
+    // grid goes in waves of one a CU; a work item takes a fixed part (its
+    // prologue, query rows and epilogue) and its blocks' time (more where two
+    // 64-row tiles load a block each); splits add the combine, by the rows it
+    // reads.  Fitted to 1300 timed calls of 3..300 jobs of 16, 64 and 128 rows
+    // x 8..600 blocks with 1..90 splits (8 % rms) and 600 of tokens.
+    const double blocks = q.by_id ? (double)((blocks_of(rg) + q.S - 1) / q.S)
+                        : a.tokens ? (double)((q.sps + 63) / 64)
+                        : a.per_row ? (double)std::min<int64_t>(std::max<int64_t>(a.NB, 1), q.sps * tile_qrows)
+                        : (double)q.sps;
+    const double fixed_us = rg == 1 ? 6.4 : a.fp8 ? 11.0 : 10.5;
+    const double block_us = rg == 1 ? (a.tokens ? (a.fp8 ? 2.9 : 4.2) : rows <= 64 ? 2.15 : a.fp8 ? 2.3 : 2.4)
+                                    : (a.tokens ? (a.fp8 ? 5.0 : 4.1) : a.fp8 ? 4.0 : 3.6);
+    const double waves = std::ceil((double)a.R * q.row_tiles * q.S / a.cus);
+    q.us = waves * (fixed_us + blocks * block_us);
+    if (q.S > 1) q.us += 1.5 + 0.3e-3 * (double)a.R * q.S * rows;
+    return q;
+  }
+
+  Plan choose() const {
+    Plan plan{};
+    if (a.n_splits > 0) {
+      for (int rg = 2; rg >= 1; --rg) {
+        if (row_groups && rg != row_groups) continue;
+        const Plan q = plan_of(rg, std::min<int64_t>(a.n_splits, std::max<int64_t>(by_id_of(rg) ? a.NB : a.K, 1)));
+        if (!plan.row_groups || q.us < plan.us) plan = q;
+      }
+      return plan;
+    }
+    // One split, or as many as one, two or three waves of workgroups hold; at
+    // least two blocks a split (one block costs less than its split's fixed
+    // part).  A grid just past a whole number of waves costs a wave more: 20
+    // jobs of 128 rows x 200 blocks take 122 us in 13 splits (260 workgroups)
+    // and 85 in 12, 40 x 600 blocks 622 and 420 (fp8 708 and 446), 24 of 2048
+    // tokens 67 and 39.  Several waves of shorter splits where one wave leaves
+    // CUs idle, and are taken where they promise 7 % and more: 300 jobs of 64
+    // rows x 64 blocks 305 us in one split, 266 in three.  A fourth wave gains
+    // nothing over the sizes above.
+    // A plan whose split rows fit the allocation-free entry's scratch (64 MiB)
+    // goes before one whose rows do not, for every entry; where a list's limit
+    // leaves none that fits, the cheapest is taken: 256 jobs of 128 rows x 2048
+    // tokens, two splits at least, take 395 us in 64-row tiles and 211 in 128-row
+    // ones, and their split rows are the same 65 MiB.
+    // Two splits of at most two blocks save at most two blocks' time and add
+    // the combine's launch: one split does better (4 blocks of one 16-row
+    // job: 12.4 us in one split against 14.9 in two).
+    for (int rg = 1; rg <= 2; ++rg) {
+      if (row_groups && rg != row_groups) continue;
+      const int64_t units = std::max<int64_t>(a.R * row_tiles_of(rg), 1);
+      const int64_t most = std::max<int64_t>(blocks_of(rg) / 2, 1);
+      for (int waves = 0; waves <= 3; ++waves) {
+        const int64_t S = std::max<int64_t>(1, std::min<int64_t>(waves * a.cus / units, most));
+        if (S == 2 && !by_id_of(rg) && Kb <= 5) continue;
+        const Plan q = plan_of(rg, S);
+        const bool first = !plan.row_groups;
+        if (!first && fits(plan) && !fits(q)) continue;
+        if (first || (fits(q) && !fits(plan)) || q.us < plan.us * (waves > 1 ? 0.93 : 1.0)) plan = q;
+      }
+    }
+    return plan;
+  }
+};
+
+}  // namespace mla
