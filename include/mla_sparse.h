@@ -177,10 +177,9 @@ mla_status_t mla_sparse_partial_attn(const mla_tensor_t* q_lat, const mla_tensor
 typedef struct {
   /* split-K: work splits per job (0 = automatic).  A shared selection, or
    * per-row selections whose K slots times the query rows of a row tile
-   * exceed 1024 (512 with an fp8 cache or 64-row tiles, which then take at
-   * least two), split into ranges of slots (1..K); other per-row selections
-   * split by logical block, split s taking blocks s, s + n, s + 2n, ...
-   * (1..NB). */
+   * exceed 1024 (512 with an fp8 cache), split into ranges of slots (1..K);
+   * other per-row selections split by logical block, split s taking blocks
+   * s, s + n, s + 2n, ... (1..NB). */
   int32_t n_splits;
   /* rows per work item: 64 or 128 (0 = automatic: 128 when Mq * H > 64 and
    * the splits are long, else 64). */

@@ -314,39 +314,8 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     if (planner.refused) return fail(MLA_ERR_UNSUPPORTED, planner.refused);
     const mla::Plan plan = planner.choose();
     const int row_groups = plan.row_groups;
-    const int64_t row_tiles = plan.row_tiles, S = plan.S, sps = plan.sps, tile_qrows = planner.tile_qrows;
+    const int64_t row_tiles = plan.row_tiles, S = plan.S, sps = plan.sps;
     const bool by_id = plan.by_id;
-    // Per-row selections of a bf16 cache in 64-row tiles whose slots fit a
-    // 128-row tile's list but not their own shorter one need two splits where
-    // one might do.  Where those exceed the allocation-free entry's scratch, the
-    // call goes job range by job range (one after the other on the stream).
-    if (no_alloc && per_row && !fp8 && row_groups == 1 && K * tile_qrows <= mla::kMaxSlotsPerSplit &&
-        !(opts && opts->n_splits > 1) && R > 1 && S > 1 && planner.ws_size(S) > (size_t)MLA_NOALLOC_SCRATCH_BYTES) {
-      const int64_t fit = std::max<int64_t>(
-          1, MLA_NOALLOC_SCRATCH_BYTES / (S * rows * (int64_t)(MLA_DLAT * sizeof(uint16_t) + 3 * sizeof(float))));
-      // as small jobs' rows may be kept in fp32: half as many
-      const int64_t step = std::max<int64_t>(1, fit / 2);
-      mla_partial_opts_t o = opts ? *opts : mla_partial_opts_t{};
-      o.row_tile = 64;
-      auto rows_from = [](const mla_tensor_t& t, int64_t first, int64_t n, int64_t bytes) {
-        mla_tensor_t v = t;
-        v.data = (char*)t.data + first * t.stride[0] * bytes;
-        v.shape[0] = n;
-        return v;
-      };
-      for (int64_t r0 = 0; r0 < R;) {
-        // jobs of one range read consecutive q rows (or all the same one)
-        const int64_t n = std::min<int64_t>(step, Rq == 1 ? R - r0 : Rq - r0 % Rq);
-        const int64_t q0 = r0 % Rq, nq = Rq == 1 ? 1 : n;
-        const mla_tensor_t ql = rows_from(*q_lat, q0, nq, 2), qp = rows_from(*q_pe, q0, nq, 2);
-        const mla_tensor_t tb = rows_from(*chunk_block_table, r0, n, 4), sl = rows_from(*sel_block_ids, r0, n, 4);
-        const mla_tensor_t ol = rows_from(*out_lat, r0, n, wire ? 2 : 4), os = rows_from(*out_lse, r0, n, 4);
-        if ((st = partial_call(&ql, &qp, ckv_pool, kpe_pool, &tb, &sl, scale, &ol, &os, &o, stream, false, true)) != MLA_OK)
-          return st;
-        r0 += n;
-      }
-      return MLA_OK;
-    }
     if (R * row_tiles * S > INT32_MAX) return fail(MLA_ERR_UNSUPPORTED, "grid too large");
 
     hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
@@ -378,6 +347,7 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     // split-major numbering once a split's row tiles fill an XCD's share of
     // the grid (below that the combine's reads of a tile's splits on one XCD
     // are worth more than the shared block loads)
+    p.long_lists = plan.long_lists ? 1 : 0;
     p.tiles_fast = by_id && row_tiles >= 8 ? 1 : 0;
     p.row_tiles = (int32_t)row_tiles;
     p.by_splits = mla::make_div(S);

@@ -63,6 +63,9 @@ struct PartialParams {
   // work items numbered row tiles fastest (per-row selections split by
   // logical block, with enough row tiles that one split's tiles fill an XCD)
   int32_t tiles_fast;
+  // 64-row tiles of per-row selections whose splits list more than
+  // kPerRowListShort entries (bf16 caches only)
+  int32_t long_lists;
   // divisors: n_splits, row_tiles, H, q_jobs, q_rep, and K (per-row selections);
   // grid8: workgroups / 8 when 8 divides them, else 0
   Div by_splits, by_tiles, by_H, by_jobs, by_rep, by_K;
@@ -155,8 +158,8 @@ constexpr int kKvFp8Split = 2;   // e4m3, separate ckv and kpe scales per block
 // its stage area, NB * (query rows of the tile) 16-bit counters.
 constexpr int kPerRowCounterBytes = 2 * 64 * 1152 - 64;  // the stage area, less the wave counters
 constexpr int kPerRowMaxRows = 64;                  // query rows per row tile (mask bits)
-// list entries per split of per-row selections with fp8 caches or 64-row tiles
-// (elsewhere kMaxSlotsPerSplit)
+// list entries per split of per-row selections with fp8 caches, and in the
+// eight-wave kernel of 64-row tiles (elsewhere kMaxSlotsPerSplit)
 constexpr int kPerRowListShort = kMaxSlotsPerSplit / 2;
 
 // 64-row tiles: the waves' requests to raise a stage's maxima, a byte per wave

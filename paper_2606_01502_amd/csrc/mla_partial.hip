@@ -749,16 +749,23 @@ __device__ __forceinline__ int compact_tokens(const PartialParams& p, int r, int
   return n_tok;
 }
 
-// ---- the 128-row kernel.
+// ---- the 128-row kernel, and the 64-row one of long per-row lists.
 //
-// RG = 2 row groups of 16 per wave: wave w computes rows 32w .. 32w+31 of the
-// row tile over all 512 latent columns.  KV is the cache
+// RG row groups of 16 per wave: wave w computes rows 16*RG*w .. 16*RG*(w+1)-1
+// of the row tile (64*RG rows) over all 512 latent columns.  KV is the cache
 // kind: bf16, e4m3 with one scale per block for the whole 576-wide entries, or
 // e4m3 with separate latent and RoPE scales per block.
-template <int KV, int SEL>
+//
+// RG = 1 serves per-row selections of a bf16 cache with 513 to 1024 entries in
+// a split's list: its LDS holds such a list beside the stages, that of the
+// eight-wave kernel below does not.  Two lists of half the length would load a
+// block that rows chose in both once for each: 64 requesters x 16 heads with
+// 200 of 400 blocks each take 85 us here and 108 in two lists, 8 jobs of 64
+// one-head requesters with 16 of 64 blocks 30 and 109; and the second split of
+// a call that needs only one takes workspace.
+template <int RG, int KV, int SEL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void partial_kernel(const PartialParams p) {
-  constexpr int RG = 2;
   constexpr bool FP8 = KV != kKvBf16;
   constexpr bool PR = SEL == kSelPerRow;   // a block selection per query row
   constexpr bool TOK = SEL == kSelTokens;  // token selections, 64 to a virtual block
@@ -2378,8 +2385,14 @@ void tile64_kernel(const PartialParams p) {
 template <int KV, int SEL = kSelShared>
 static void launch_kv(const PartialParams& p, int grid, int row_groups, hipStream_t s) {
   if (row_groups == 2) {
-    hipLaunchKernelGGL((partial_kernel<KV, SEL>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((partial_kernel<2, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
     return;
+  }
+  if constexpr (KV == kKvBf16 && SEL == kSelPerRow) {
+    if (p.long_lists) {
+      hipLaunchKernelGGL((partial_kernel<1, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
+      return;
+    }
   }
   // jobs of 32 rows at most: half a tile
   if (p.rows <= 32)

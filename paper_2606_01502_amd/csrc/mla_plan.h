@@ -25,6 +25,7 @@ struct Plan {
   int64_t row_tiles;       // tiles of a job
   int64_t S, sps;          // splits of a tile's slots, slots of a split
   bool by_id;              // splits by logical block instead of slot range
+  bool long_lists;         // 64-row tiles: lists too long for the eight-wave kernel
   double us;               // what the call should take
 };
 
@@ -89,24 +90,22 @@ struct Planner {
   uint64_t ws_size(int64_t S) const { return ws_rows_bytes(S) + 3 * split_rows(S) * 4; }
   bool fits(const Plan& q) const { return q.S <= 1 || ws_size(q.S) <= kPlanScratch; }
 
-  // entries one split's list holds (per-row selections with an fp8 cache or
-  // 64-row tiles: a shorter one, see the kernel's LDS layout)
-  int64_t list_cap_of(int rg) const {
-    return a.per_row && (a.fp8 || rg == 1) ? kPerRowListShort : kMaxSlotsPerSplit;
-  }
+  // entries one split's list holds (per-row selections with an fp8 cache: a
+  // shorter one, see the kernel's LDS layout)
+  int64_t list_cap() const { return a.per_row && a.fp8 ? kPerRowListShort : kMaxSlotsPerSplit; }
   // per-row selections whose tile slots all fit one list split by logical
   // block: every split then scans all slots and the rows that chose a block
   // in different slots still share its load
-  bool by_id_of(int rg) const { return a.per_row && tile_qrows > 1 && a.K * tile_qrows <= list_cap_of(rg); }
+  bool by_id() const { return a.per_row && tile_qrows > 1 && a.K * tile_qrows <= list_cap(); }
   // the most blocks a tile can visit
-  int64_t blocks_of(int rg) const { return by_id_of(rg) ? std::min<int64_t>(a.NB, a.K * tile_qrows) : Kb; }
+  int64_t most_blocks() const { return by_id() ? std::min<int64_t>(a.NB, a.K * tile_qrows) : Kb; }
 
   // the plan of about S splits with tiles of rg row groups, and its time
   Plan plan_of(int rg, int64_t S) const {
-    Plan q{rg, row_tiles_of(rg), S, a.K, by_id_of(rg), 0.0};
-    const int64_t list_cap = list_cap_of(rg);
-    // a split's block list holds at most list_cap entries: its slots, or for
+    Plan q{rg, row_tiles_of(rg), S, a.K, by_id(), false, 0.0};
+    // a split's block list holds at most so many entries: its slots, or for
     // per-row selections its slots of every query row of the tile
+    const int64_t cap = list_cap();
     if (a.tokens) {
       // whole virtual blocks per split, at most one list of tokens
       S = std::max<int64_t>(S, (a.K + kMaxSlotsPerSplit - 1) / kMaxSlotsPerSplit);
@@ -114,18 +113,19 @@ struct Planner {
       q.sps = std::min<int64_t>(q.sps, kMaxSlotsPerSplit);
       q.S = std::max<int64_t>(1, (a.K + q.sps - 1) / q.sps);
     } else if (!q.by_id) {
-      S = std::max<int64_t>(S, (a.K * tile_qrows + list_cap - 1) / list_cap);
+      S = std::max<int64_t>(S, (a.K * tile_qrows + cap - 1) / cap);
       q.sps = std::max<int64_t>(1, (a.K + S - 1) / S);
-      if (a.per_row) q.sps = std::min<int64_t>(q.sps, std::max<int64_t>(1, list_cap / tile_qrows));
+      if (a.per_row) q.sps = std::min<int64_t>(q.sps, std::max<int64_t>(1, cap / tile_qrows));
       q.S = std::max<int64_t>(1, (a.K + q.sps - 1) / q.sps);
     }
+    q.long_lists = a.per_row && !a.fp8 && rg == 1 && q.sps * tile_qrows > kPerRowListShort;
     // What a call takes, microseconds.  A workgroup fills its CU, so that a
     // grid goes in waves of one a CU; a work item takes a fixed part (its
     // prologue, query rows and epilogue) and its blocks' time (more where two
     // 64-row tiles load a block each); splits add the combine, by the rows it
     // reads.  Fitted to 1300 timed calls of 3..300 jobs of 16, 64 and 128 rows
     // x 8..600 blocks with 1..90 splits (8 % rms) and 600 of tokens.
-    const double blocks = q.by_id ? (double)((blocks_of(rg) + q.S - 1) / q.S)
+    const double blocks = q.by_id ? (double)((most_blocks() + q.S - 1) / q.S)
                         : a.tokens ? (double)((q.sps + 63) / 64)
                         : a.per_row ? (double)std::min<int64_t>(std::max<int64_t>(a.NB, 1), q.sps * tile_qrows)
                         : (double)q.sps;
@@ -143,7 +143,7 @@ struct Planner {
     if (a.n_splits > 0) {
       for (int rg = 2; rg >= 1; --rg) {
         if (row_groups && rg != row_groups) continue;
-        const Plan q = plan_of(rg, std::min<int64_t>(a.n_splits, std::max<int64_t>(by_id_of(rg) ? a.NB : a.K, 1)));
+        const Plan q = plan_of(rg, std::min<int64_t>(a.n_splits, std::max<int64_t>(by_id() ? a.NB : a.K, 1)));
         if (!plan.row_groups || q.us < plan.us) plan = q;
       }
       return plan;
@@ -168,10 +168,10 @@ struct Planner {
     for (int rg = 1; rg <= 2; ++rg) {
       if (row_groups && rg != row_groups) continue;
       const int64_t units = std::max<int64_t>(a.R * row_tiles_of(rg), 1);
-      const int64_t most = std::max<int64_t>(blocks_of(rg) / 2, 1);
+      const int64_t most = std::max<int64_t>(most_blocks() / 2, 1);
       for (int waves = 0; waves <= 3; ++waves) {
         const int64_t S = std::max<int64_t>(1, std::min<int64_t>(waves * a.cus / units, most));
-        if (S == 2 && !by_id_of(rg) && Kb <= 5) continue;
+        if (S == 2 && !by_id() && Kb <= 5) continue;
         const Plan q = plan_of(rg, S);
         const bool first = !plan.row_groups;
         if (!first && fits(plan) && !fits(q)) continue;

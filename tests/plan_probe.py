@@ -14,9 +14,10 @@ _MAIN = r"""
 #include "mla_plan.h"
 #include <cstdio>
 static void show(const mla::Planner& p, const mla::Plan& q) {
-  std::printf(" %d %lld %lld %lld %d %.17g %d %llu", q.row_groups, (long long)q.row_tiles,
+  std::printf(" %d %lld %lld %lld %d %.17g %d %llu %d %lld", q.row_groups, (long long)q.row_tiles,
               (long long)q.S, (long long)q.sps, (int)q.by_id, q.us, (int)p.ws_half(q.S),
-              (unsigned long long)(q.S > 1 ? p.ws_size(q.S) : 0));
+              (unsigned long long)(q.S > 1 ? p.ws_size(q.S) : 0),
+              (int)q.long_lists, (long long)p.tile_qrows);
 }
 int main() {
   long long R, Mq, H, NB, K, tok, pr, fp8, ns, rt, rg, S;
@@ -61,6 +62,8 @@ class Plan:
     us: float
     half: bool
     ws: int
+    long_lists: bool
+    tile_qrows: int
 
 
 def build(tmp):
@@ -74,14 +77,15 @@ def build(tmp):
 
 
 def _parse(v):
-    return Plan(int(v[0]), int(v[1]), int(v[2]), int(v[3]), v[4] == "1", float(v[5]), v[6] == "1", int(v[7]))
+    return Plan(int(v[0]), int(v[1]), int(v[2]), int(v[3]), v[4] == "1", float(v[5]), v[6] == "1", int(v[7]),
+                v[8] == "1", int(v[9]))
 
 
 def plans(exe, calls, beside=None):
     """[(plan, plan of beside[i] = (row groups, splits) or None)], None where refused."""
     lines = []
     for i, c in enumerate(calls):
-        rg, S = beside[i] if beside and beside[i] else (0, 0)
+        rg, S = beside[i][:2] if beside and beside[i] else (0, 0)
         lines.append(f"{c.R} {c.Mq} {c.H} {c.NB} {c.K} {int(c.tokens)} {int(c.per_row)} {int(c.fp8)} "
                      f"{c.n_splits} {c.row_tile} {rg} {S}")
     out = subprocess.run([exe], input="\n".join(lines) + "\n", check=True, capture_output=True, text=True)
@@ -90,12 +94,12 @@ def plans(exe, calls, beside=None):
     res = []
     for ln in rows:
         v = ln.split()
-        res.append(None if v[0] == "refused" else (_parse(v[:8]), _parse(v[8:16]) if len(v) > 8 else None))
+        res.append(None if v[0] == "refused" else (_parse(v[:10]), _parse(v[10:]) if len(v) > 10 else None))
     return res
 
 
 def cover_rule(c):
-    """Row groups and splits by coverage: 128-row tiles where a job has more
+    """(row groups, splits, whether splits go by logical block) by coverage: 128-row tiles where a job has more
     than 64 rows and the splits hold 8 blocks and more, and the smallest number
     of splits of at least two blocks that gives every compute unit a workgroup."""
     Kb = (c.K + 63) // 64 if c.tokens else c.K
@@ -124,7 +128,7 @@ def cover_rule(c):
     S = max(1, (CUS + units - 1) // units)
     cap = 512 if c.per_row and c.fp8 else 1024
     if c.per_row and tq > 1 and c.K * tq <= cap:
-        return rg, min(S, max(min(c.NB, c.K * tq) // 2, 1))
+        return rg, min(S, max(min(c.NB, c.K * tq) // 2, 1)), True
     S = min(S, max(Kb // 2, 1))
     if S == 2 and Kb <= 5:
         S = 1
@@ -136,7 +140,7 @@ def cover_rule(c):
         sps = max(1, (c.K + S - 1) // S)
         if c.per_row:
             sps = min(sps, max(1, cap // tq))
-    return rg, max(1, (c.K + sps - 1) // sps)
+    return rg, max(1, (c.K + sps - 1) // sps), False
 
 
 def draw(rng, kinds=("blocks", "tokens", "per_row")):

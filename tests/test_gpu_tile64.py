@@ -114,8 +114,8 @@ def test_half_tiles(mq, h, kv, kind):
 
 @pytest.mark.parametrize("shared_q", [False, True])
 def test_per_row_lists_beyond_the_scratch(shared_q):
-    # 64 query rows x 16 slots a tile: two splits, whose rows exceed the
-    # allocation-free entry's scratch for all jobs together
+    # 64 query rows x 16 slots a tile, a full list: in two splits the rows of all
+    # jobs together would exceed the allocation-free entry's scratch
     R, Mq, K, NB = 600, 64, 16, 24
     print(f"case: per-row beyond scratch shared_q={shared_q}", flush=True)
     w = W.random_case(1100, R=R, Mq=Mq, H=1, P=40, NB=NB, K=K, per_row=True)
@@ -131,3 +131,39 @@ def test_per_row_lists_beyond_the_scratch(shared_q):
         assert float(err.max()) <= 2 * (2 ** -8 + 2 ** -11), float(err.max())
         same = (lse == ref_l) | ((lse - ref_l).abs() <= 1e-4)
         assert bool(same.all())
+
+
+@pytest.mark.parametrize("mq,h,k", [(8, 8, 64), (8, 8, 65), (16, 4, 64), (8, 8, 128), (8, 8, 129),
+                                    (3, 64, 512), (3, 64, 513), (70, 1, 8), (70, 1, 9)])
+def test_long_per_row_lists(mq, h, k):
+    # a tile's slots at and past 512 (the eight-wave kernel's list) and 1024 (the
+    # longest: ranges of slots from there on)
+    w = W.random_case(1130 + mq + k, R=2, Mq=mq, H=h, P=80, NB=2 * k + 3 if h < 64 else 600, K=k,
+                      per_row=True, shared_frac=0.5, allow_dup=True)
+    for ns in (0, 1, 3):
+        _check(w, f"long list {mq}x{h} K={k} splits={ns}", n_splits=ns)
+
+
+@pytest.mark.parametrize("R,Mq,H,K,NB,n_q", [(300, 4, 16, 400, 500, 300), (200, 8, 8, 400, 600, 2),
+                                             (1, 32768, 1, 12, 24, 1)])
+def test_allocation_free_calls_with_long_lists(R, Mq, H, K, NB, n_q):
+    # many jobs, jobs that share few query rows, and one job of many rows
+    print(f"case: no_alloc R={R} Mq={Mq} H={H} K={K} n_q={n_q}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1150 + R)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda").bfloat16()
+
+    P = 700
+    q_lat, q_pe, ckv, kpe = normal(n_q, Mq, H, 512), normal(n_q, Mq, H, 64), normal(P, 64, 512), normal(P, 64, 64)
+    table = torch.stack([torch.randperm(P, generator=g, device="cuda")[:NB] for _ in range(R)]).int()
+    sel = torch.rand((R, Mq, NB), generator=g, device="cuda").topk(K).indices.int()
+    out, lse = mla.sparse_partial_attn(q_lat, q_pe, ckv, kpe, table, sel, 576 ** -0.5, no_alloc=True)
+    torch.cuda.synchronize()
+    for r, i in ((0, 0), (R - 1, Mq - 1), (R // 2, Mq // 2)):
+        blk = table[r][sel[r, i].long()].long()
+        k_lat, k_pe = ckv[blk].reshape(-1, 512).double().cpu(), kpe[blk].reshape(-1, 64).double().cpu()
+        s = (q_lat[r % n_q, i].double().cpu() @ k_lat.T + q_pe[r % n_q, i].double().cpu() @ k_pe.T) * 576 ** -0.5
+        G.assert_parity(out[r, i].double().cpu().numpy(), lse[r, i].double().cpu().numpy(),
+                        (torch.softmax(s, -1) @ k_lat).numpy(), torch.logsumexp(s, -1).numpy(), f"job {r} row {i}")
