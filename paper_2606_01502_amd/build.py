@@ -4,7 +4,8 @@ Each csrc/*.hip file is compiled separately (in parallel) and linked into
 paper_2606_01502_amd/libmla_sparse.so.  Packed-FP32 instructions are
 disabled for every device compile.  The device assembly of every source is
 generated beside the objects and checked for matrix-core wait-state hazards
-around the inline-asm products (hazards.py); a hazard fails the build.
+around the inline-asm products and for registers kept in scratch memory
+(hazards.py); either fails the build.
 """
 import glob
 import os
@@ -50,14 +51,19 @@ def _device_asm(src, extra=()):
 
 
 def check_hazards(asm_files):
-    """Raise if the device assembly has a wait-state hazard (see hazards.py)."""
+    """Raise if the device assembly has a wait-state hazard or a kernel keeps
+    registers in scratch memory (see hazards.py)."""
     if ROOT not in sys.path:
         sys.path.insert(0, ROOT)
     from paper_2606_01502_amd import hazards
-    bad = []
+    bad, spilled = [], []
     for f in asm_files:
         with open(f) as fh:
-            bad += [f"{os.path.basename(f)}: {v}" for v in hazards.check(fh.read())]
+            text = fh.read()
+        bad += [f"{os.path.basename(f)}: {v}" for v in hazards.check(text)]
+        spilled += hazards.scratch(text)
+    if spilled:
+        raise RuntimeError("registers in scratch memory:\n" + "\n".join(spilled[:20]))
     if bad:
         raise RuntimeError("matrix-core wait-state hazards in the device code:\n" +
                            "\n".join(bad[:20]))

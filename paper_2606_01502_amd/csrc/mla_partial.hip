@@ -1590,11 +1590,16 @@ template <bool FP8, bool TOK>
 struct Issue32 {
   using L = Tile<FP8, false>;
   static constexpr int kLat = L::kLoads - 1;
-  uint32_t lat[kLat], rope;
+  // (token selections, where registers are short, hold the first latent load's
+  // offset only, the others being one XOR away, and fp8 ones the wave's part of
+  // the RoPE load's)
+  static constexpr int kHeld = TOK ? 1 : kLat;
+  uint32_t lat[kHeld], rope;
   const uint8_t* ckv;  // the wave's first row
   const uint8_t* kpe;
   uint32_t lds_lat, lds_rope;  // LDS addresses of the wave's first rows
-  int tok, tok_rope;  // TOK: pool tokens of stage tokens 4w + (lane & 3) and of the RoPE load's row
+  // TOK: pool tokens of stage token 4w + (lane & 3) and (fp8) of the RoPE load's row
+  int tok, tok_rope;
 
   __device__ __forceinline__ Issue32(const PartialParams& p, int wave, int lane) {
     ckv = p.ckv;
@@ -1605,20 +1610,17 @@ struct Issue32 {
     const int kw = (b3 << 1) | (wave >> 2);   // their key32, less the low bits' part
     const int hi = lane >> 5;
 #pragma unroll
-    for (int k = 0; k < kLat; ++k)
+    for (int k = 0; k < kHeld; ++k)
       lat[k] = FP8 ? (uint32_t)(hi * 512 + (((lane & 31) ^ (hi << 2) ^ kw ^ (k << 3)) << 4))
                    : (uint32_t)((lane ^ kw ^ (k << 2)) << 4);
-    rope = FP8 ? (uint32_t)((lane >> 2) * 64 + (((lane & 3) ^ (b3 << 1)) << 4))
+    rope = FP8 && TOK ? (uint32_t)(b3 << 5)
+         : FP8 ? (uint32_t)((lane >> 2) * 64 + (((lane & 3) ^ (b3 << 1)) << 4))
                : (uint32_t)((lane >> 3) * 128 + (((lane & 7) ^ ((((lane >> 4) & 1) << 1) | (b3 << 2))) << 4));
   }
   // what aim() needs of the list for half block h, read ahead of it
   __device__ __forceinline__ void look(const LDS int* list, int h, int wave, int lane, int (&e)[2]) const {
-    if constexpr (TOK) {
-      e[0] = list[h * 32 + 4 * wave + (lane & 3)];
-      e[1] = list[h * 32 + 4 * wave + ((FP8 ? lane >> 2 : lane >> 3) & 3)];
-    } else {
-      e[0] = list[h >> 1];
-    }
+    e[0] = TOK ? list[h * 32 + 4 * wave + (lane & 3)] : list[h >> 1];
+    if constexpr (TOK && FP8) e[1] = list[h * 32 + 4 * wave + ((lane >> 2) & 3)];
   }
   // points the loads at half block h and stage buf
   __device__ __forceinline__ void aim(const PartialParams& p, const int (&e)[2], int h, uint32_t buf, int wave) {
@@ -1641,6 +1643,9 @@ struct Issue32 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                  :: "v"(a), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
   }
+  __device__ __forceinline__ uint32_t lat_of(int j) const {
+    return (uint32_t)lds_opaque((int)lat[0]) ^ (uint32_t)(j << (FP8 ? 7 : 6));
+  }
   // Load j; every lane of the wave is active where this is called.
   __device__ __forceinline__ void load(const PartialParams& p, int j, int lane) const {
     if (j < kLat) {
@@ -1650,10 +1655,10 @@ struct Issue32 {
                      : "memory", "m0");
       } else if constexpr (FP8) {
         const uint32_t t = (uint32_t)__shfl(tok, 2 * j + (lane >> 5));
-        go64(p.ckv + (uint64_t)t * 512u + (lat[j] & 0x1f0u), lds_lat + (uint32_t)j * 1024u);
+        go64(p.ckv + (uint64_t)t * 512u + ((lat_of(j)) & 0x1f0u), lds_lat + (uint32_t)j * 1024u);
       } else {
         const uint32_t t = (uint32_t)__builtin_amdgcn_readlane(tok, j);
-        go(lat[j], p.ckv + (uint64_t)t * 1024u, lds_lat + (uint32_t)j * 1024u);
+        go(lat_of(j), p.ckv + (uint64_t)t * 1024u, lds_lat + (uint32_t)j * 1024u);
       }
     } else {
       // the first 32 (fp8: 16) lanes only
@@ -1663,7 +1668,9 @@ struct Issue32 {
                      :: "v"(rope), "s"(uniform(kpe)), "s"(__builtin_amdgcn_readfirstlane(lds_rope)), "s"(kLanes)
                      : "memory", "m0");
       } else {
-        const uint8_t* a = p.kpe + (uint64_t)(uint32_t)tok_rope * L::kRopeRow + (rope & (FP8 ? 0x30u : 0x70u));
+        const uint32_t t = (uint32_t)(FP8 ? tok_rope : __shfl(tok, (lane >> 3) & 3));
+        const uint32_t o = FP8 ? rope ^ ((uint32_t)(lds_opaque(lane) & 3) << 4) : rope & 0x70u;
+        const uint8_t* a = p.kpe + (uint64_t)t * L::kRopeRow + o;
         asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
                      :: "v"(a), "s"(__builtin_amdgcn_readfirstlane(lds_rope)), "s"(kLanes) : "memory", "m0");
       }
@@ -1790,7 +1797,7 @@ void tile64_kernel(const PartialParams p) {
   const int n = TOK ? (n_tok + 31) / 32 : 2 * n_valid;  // stages of tokens
 
   Issue32<FP8, TOK> is(p, wave, lane);
-  int ahead[2] = {0, 0};  // the list entry of the stage to load next
+  int ahead[2] = {0, 0};  // the list entries of the stage to load next
   auto aim = [&](int h) { is.aim(p, ahead, h, lds0 + (uint32_t)((h % L::kNum) * L::kStage), wave); };
   auto issue = [&](int h) {
     if (h >= n) return;
@@ -2019,7 +2026,10 @@ void tile64_kernel(const PartialParams p) {
   // Step i up to the scores of stage i + 1.  kMid (not the first step): with
   // the last value products of stage i - 1, and the first reads of stage i's
   // values and weights
-  constexpr int kAhead = FP8 ? 3 : 6;  // key reads in flight ahead of their products
+  // key reads in flight ahead of their products (fewer where the tokens' rows
+  // take registers: a spilled query fragment would be read back in every stage,
+  // with a wait for all loads in flight)
+  constexpr int kAhead = TOK && NK == 2 ? (FP8 ? (kSplitScales ? 2 : 3) : 5) : FP8 ? 3 : 6;
   auto scores = [&](int i, auto mid) -> u32x2_t {
     constexpr bool kMid = decltype(mid)::value;
     const uint32_t st = (uint32_t)(((i + 1) % L::kNum) * L::kStage);
@@ -2088,7 +2098,8 @@ void tile64_kernel(const PartialParams p) {
           }
           if constexpr (PR) s_mask = masks[(i + 1) >> 1];
         }
-        if (step == 5) is.look(list, ih + 1, wave, lane, ahead);
+        // (tokens: after the stage's last load, which reads the same register)
+        if (step == (TOK ? 15 : 5)) is.look(list, ih + 1, wave, lane, ahead);
         if constexpr (kMid) {
           if (step == 12) pload(i, 0);
           if (step >= 13 && step < 13 + kPvAhead) vload(step - 13);

@@ -205,6 +205,20 @@ def check(text, window=20):
     return out
 
 
+def scratch(text):
+    """Kernels that keep registers in scratch memory: 'name: bytes'.  The
+    kernels count their own loads in flight; a value read back from scratch
+    waits for all of them, and the compiler says nothing about it."""
+    out, name = [], None
+    for line in text.splitlines():
+        m = re.match(r"\s+\.amdhsa_(kernel|private_segment_fixed_size) (\S+)", line)
+        if m and m.group(1) == "kernel":
+            name = m.group(2)
+        elif m and int(m.group(2)):
+            out.append(f"{name}: {m.group(2)} bytes of scratch")
+    return out
+
+
 if __name__ == "__main__":
     bad = check(open(sys.argv[1]).read())
     print("\n".join(bad[:200]))

@@ -87,6 +87,12 @@ def test_paths_through_branches():
     assert Z.check(text) == []
 
 
+def test_scratch_is_reported():
+    text = ("\t.amdhsa_kernel _Za\n\t\t.amdhsa_private_segment_fixed_size 0\n\t.end_amdhsa_kernel\n"
+            "\t.amdhsa_kernel _Zb\n\t\t.amdhsa_private_segment_fixed_size 52\n\t.end_amdhsa_kernel\n")
+    assert Z.scratch(text) == ["_Zb: 52 bytes of scratch"]
+
+
 def test_library_device_code_is_clean(tmp_path):
     """Every kernel of the library, compiled here for gfx950."""
     if shutil.which(B.HIPCC) is None and not os.path.exists(B.HIPCC):
