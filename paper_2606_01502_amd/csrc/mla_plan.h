@@ -39,33 +39,45 @@ struct Planner {
   int64_t tile_qrows = 1;  // per-row selections: query rows a tile spans (one mask bit each)
   int row_groups = 0;      // of every plan, or 0: either
   const char* refused = nullptr;
+  Plan cover{};            // the fewest splits that give every compute unit a workgroup
 
   explicit Planner(const PlanArgs& args) : a(args), rows(a.Mq * a.H) {
     Kb = a.tokens ? (a.K + 63) / 64 : a.K;  // a token selection's slots fill K / 64 blocks
-    // the row groups of a tile: the caller's; 1 where a job has no more rows; 2
-    // for per-row selections whose splits are long (8 blocks and more), where a
-    // tile of twice the rows shares more loads; 0: the cheaper
+    // the row groups of the covering plan: the caller's; 1 where a job has no
+    // more rows; 2 where splits are long (8 blocks and more).  Per-row selections
+    // keep to them, for a tile of twice the rows shares more loads; elsewhere the
+    // cheaper is taken
+    int groups = 1;
     if (a.row_tile) {
-      row_groups = a.row_tile / 64;
-    } else if (rows <= 64) {
-      row_groups = 1;
-    } else if (a.per_row) {
+      groups = a.row_tile / 64;
+    } else if (rows > 64) {
       const int64_t units2 = a.R * row_tiles_of(2);
       const int64_t s2 = std::min<int64_t>((a.cus + units2 - 1) / units2, std::max<int64_t>(Kb / 2, 1));
-      row_groups = Kb < 8 * s2 ? 1 : 2;
+      groups = Kb < 8 * s2 ? 1 : 2;
     }
-    if (!a.per_row) return;
-    if (row_groups == 2 && tile_query_rows(2) > kPerRowMaxRows) {
-      if (a.row_tile == 128) {
-        refused = "per-row selections: too many query rows per 128-row tile";
-        return;
+    if (a.per_row) {
+      if (groups == 2 && tile_query_rows(2) > kPerRowMaxRows) {
+        if (a.row_tile == 128) {
+          refused = "per-row selections: too many query rows per 128-row tile";
+          return;
+        }
+        groups = 1;
       }
-      row_groups = 1;
+      tile_qrows = tile_query_rows(groups);
+      if (tile_qrows > kPerRowMaxRows) refused = "per-row selections: too many query rows per tile";
+      else if (a.NB * tile_qrows * 2 > kPerRowCounterBytes)
+        refused = "per-row selections: NB x query rows per tile too large";
+      if (refused) return;
     }
-    tile_qrows = tile_query_rows(row_groups);
-    if (tile_qrows > kPerRowMaxRows) refused = "per-row selections: too many query rows per tile";
-    else if (a.NB * tile_qrows * 2 > kPerRowCounterBytes)
-      refused = "per-row selections: NB x query rows per tile too large";
+    row_groups = a.row_tile || rows <= 64 || a.per_row ? groups : 0;
+    // at least two blocks a split: one block costs less than its split's fixed
+    // part.  Two splits of at most two blocks save at most two blocks' time and
+    // add the combine's launch: one split does better (4 blocks of one 16-row
+    // job: 12.4 us in one split against 14.9 in two)
+    const int64_t units = std::max<int64_t>(a.R * row_tiles_of(groups), 1);
+    int64_t S = std::min<int64_t>((a.cus + units - 1) / units, std::max<int64_t>(most_blocks() / 2, 1));
+    if (S == 2 && !by_id() && Kb <= 5) S = 1;
+    cover = plan_of(groups, std::max<int64_t>(S, 1));
   }
 
   int64_t row_tiles_of(int rg) const { return (rows + 64 * rg - 1) / (64 * rg); }
@@ -121,20 +133,35 @@ struct Planner {
     q.long_lists = a.per_row && !a.fp8 && rg == 1 && q.sps * tile_qrows > kPerRowListShort;
     // What a call takes, microseconds.  A workgroup fills its CU, so that a
     // grid goes in waves of one a CU; a work item takes a fixed part (its
-    // prologue, query rows and epilogue) and its blocks' time (more where two
-    // 64-row tiles load a block each); splits add the combine, by the rows it
-    // reads.  Fitted to 1300 timed calls of 3..300 jobs of 16, 64 and 128 rows
-    // x 8..600 blocks with 1..90 splits (8 % rms) and 600 of tokens.
+    // prologue, query rows and epilogue) and its blocks' time, and all together
+    // no less than their bytes take from memory (each tile of a job loads its
+    // blocks; the rows' own bytes are left out, with them the prices order plans
+    // worse); splits add the combine, by the bytes of the rows it reads.
+    // Fitted to 140000 timed plans of 28000 calls of 1..700 jobs of 8..256 rows x
+    // 1..1500 blocks or 16..6000 tokens (9 % rms in 128-row tiles, 9 to 17 % in
+    // 64-row ones).
     const double blocks = q.by_id ? (double)((most_blocks() + q.S - 1) / q.S)
                         : a.tokens ? (double)((q.sps + 63) / 64)
                         : a.per_row ? (double)std::min<int64_t>(std::max<int64_t>(a.NB, 1), q.sps * tile_qrows)
                         : (double)q.sps;
-    const double fixed_us = rg == 1 ? 6.4 : a.fp8 ? 11.0 : 10.5;
-    const double block_us = rg == 1 ? (a.tokens ? (a.fp8 ? 2.9 : 4.2) : rows <= 64 ? 2.15 : a.fp8 ? 2.3 : 2.4)
-                                    : (a.tokens ? (a.fp8 ? 5.0 : 4.1) : a.fp8 ? 4.0 : 3.6);
+    struct Rate {
+      double fixed, block, bytes;  // us, us, bytes a us
+    };
+    // by selection, cache and tile: half of a 64-row tile, one for all rows,
+    // one of several, 128 rows
+    static constexpr Rate kRate[2][2][4] = {
+        {{{6.1, 1.63, 5.5e6}, {8.3, 1.85, 5.1e6}, {8.7, 1.89, 6.8e6}, {14.4, 3.30, 4.2e6}},
+         {{6.6, 1.87, 5.5e6}, {9.4, 2.32, 5.5e6}, {9.4, 2.30, 5.5e6}, {14.1, 4.16, 5.5e6}}},
+        {{{5.2, 2.00, 5.4e6}, {8.0, 2.17, 4.7e6}, {8.6, 2.11, 6.4e6}, {14.2, 3.78, 5.2e6}},
+         {{5.7, 2.38, 5.5e6}, {8.4, 2.64, 5.5e6}, {9.2, 2.49, 5.5e6}, {14.5, 4.89, 5.5e6}}}};
+    const Rate& rate = kRate[a.tokens][a.fp8][rg == 2 ? 3 : rows <= 32 ? 0 : rows <= 64 ? 1 : 2];
     const double waves = std::ceil((double)a.R * q.row_tiles * q.S / a.cus);
-    q.us = waves * (fixed_us + blocks * block_us);
-    if (q.S > 1) q.us += 1.5 + 0.3e-3 * (double)a.R * q.S * rows;
+    q.us = waves * (rate.fixed + blocks * rate.block);
+    // (rows with selections of their own share blocks, nobody here knows which)
+    if (!a.per_row)
+      q.us = std::max(q.us, rate.fixed + (double)a.R * q.row_tiles * Kb * kBlock * (kDLat + kDPe) *
+                                (a.fp8 ? 1 : 2) / rate.bytes);
+    if (q.S > 1) q.us += 1.8 + 0.4e-6 * (double)ws_rows_bytes(q.S);
     return q;
   }
 
@@ -148,23 +175,29 @@ struct Planner {
       }
       return plan;
     }
-    // One split, or as many as one, two or three waves of workgroups hold; at
-    // least two blocks a split (one block costs less than its split's fixed
-    // part).  A grid just past a whole number of waves costs a wave more: 20
-    // jobs of 128 rows x 200 blocks take 122 us in 13 splits (260 workgroups)
-    // and 85 in 12, 40 x 600 blocks 622 and 420 (fp8 708 and 446), 24 of 2048
-    // tokens 67 and 39.  Several waves of shorter splits where one wave leaves
-    // CUs idle, and are taken where they promise 7 % and more: 300 jobs of 64
-    // rows x 64 blocks 305 us in one split, 266 in three.  A fourth wave gains
-    // nothing over the sizes above.
+    // The covering plan, one split, or as many as one, two or three waves of
+    // workgroups hold.  A grid just past a whole number of waves costs a wave
+    // more: 20 jobs of 128 rows x 200 blocks take 122 us in 13 splits (260
+    // workgroups) and 85 in 12, 40 x 600 blocks 622 and 420 (fp8 708 and 446), 24
+    // of 2048 tokens 67 and 39.  Several waves of shorter splits where one wave
+    // leaves CUs idle: 281 jobs of 8 rows x 86 fp8 blocks 327 us in one split,
+    // 241 in three.  A plan has to promise 3 % over the covering one, about what
+    // the prices are off between plans of one call: over the timed calls one in
+    // 2000 then takes 2 % more than in the covering plan, and the mean is 8.7 %
+    // less (9.5 with the best plan of each call; a fourth wave adds nothing).
     // A plan whose split rows fit the allocation-free entry's scratch (64 MiB)
     // goes before one whose rows do not, for every entry; where a list's limit
     // leaves none that fits, the cheapest is taken: 256 jobs of 128 rows x 2048
     // tokens, two splits at least, take 395 us in 64-row tiles and 211 in 128-row
     // ones, and their split rows are the same 65 MiB.
-    // Two splits of at most two blocks save at most two blocks' time and add
-    // the combine's launch: one split does better (4 blocks of one 16-row
-    // job: 12.4 us in one split against 14.9 in two).
+    // Per-row selections in ranges of slots keep the covering plan: a block that
+    // rows chose in different slots is loaded once a range, so that other ranges
+    // mean other loads, which only the ids tell (28 jobs of 10 x 16 rows with 144
+    // blocks each: 268 us in four ranges, priced cheaper, 241 in the covering
+    // five).
+    plan = cover;
+    if (a.per_row && tile_qrows > 1 && !by_id()) return plan;
+    double best = 0.97 * cover.us;
     for (int rg = 1; rg <= 2; ++rg) {
       if (row_groups && rg != row_groups) continue;
       const int64_t units = std::max<int64_t>(a.R * row_tiles_of(rg), 1);
@@ -173,9 +206,11 @@ struct Planner {
         const int64_t S = std::max<int64_t>(1, std::min<int64_t>(waves * a.cus / units, most));
         if (S == 2 && !by_id() && Kb <= 5) continue;
         const Plan q = plan_of(rg, S);
-        const bool first = !plan.row_groups;
-        if (!first && fits(plan) && !fits(q)) continue;
-        if (first || (fits(q) && !fits(plan)) || q.us < plan.us * (waves > 1 ? 0.93 : 1.0)) plan = q;
+        if (fits(plan) && !fits(q)) continue;
+        if ((fits(q) && !fits(plan)) || q.us < best) {
+          plan = q;
+          best = q.us;
+        }
       }
     }
     return plan;

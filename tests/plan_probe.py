@@ -26,6 +26,7 @@ int main() {
     const mla::Planner p({R, Mq, H, NB, K, tok != 0, pr != 0, fp8 != 0, (int)ns, (int)rt, 256});
     if (p.refused) { std::printf("refused\n"); continue; }
     show(p, p.choose());
+    show(p, p.cover);
     // the plan of S splits and rg row groups beside it
     if (rg) show(p, p.plan_of((int)rg, S));
     std::printf("\n");
@@ -82,7 +83,8 @@ def _parse(v):
 
 
 def plans(exe, calls, beside=None):
-    """[(plan, plan of beside[i] = (row groups, splits) or None)], None where refused."""
+    """[(plan, the covering plan, the plan of beside[i] = (row groups, splits) or
+    None)], None where refused."""
     lines = []
     for i, c in enumerate(calls):
         rg, S = beside[i][:2] if beside and beside[i] else (0, 0)
@@ -94,7 +96,7 @@ def plans(exe, calls, beside=None):
     res = []
     for ln in rows:
         v = ln.split()
-        res.append(None if v[0] == "refused" else (_parse(v[:10]), _parse(v[10:]) if len(v) > 10 else None))
+        res.append(None if v[0] == "refused" else (_parse(v[:10]), _parse(v[10:20]), _parse(v[20:]) if len(v) > 20 else None))
     return res
 
 

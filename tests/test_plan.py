@@ -21,23 +21,32 @@ def _small(p):
     return p.ws <= P.SCRATCH
 
 
+def test_covering_plan_is_the_rule(exe):
+    calls = _calls(4, 6000)
+    for c, b, got in zip(calls, map(P.cover_rule, calls), P.plans(exe, calls)):
+        if got is not None:
+            assert (got[1].row_groups, got[1].S, got[1].by_id) == b, (c, b, got[1])
+
+
 def test_no_dearer_than_covering_the_chip(exe):
     """No plan is dearer, at the planner's own prices, than the smallest number
     of splits that covers the chip, in the tile that goes with it, where both
-    keep their split rows within the scratch array or neither does.  (A plan of
-    several waves has to promise 7 %.)"""
+    keep their split rows within the scratch array or neither does; and another
+    plan than that promises 3 %."""
     calls = [P.Call(256, 1, 128, 128, 2048, tokens=True), P.Call(256, 1, 128, 128, 2048, tokens=True, fp8=True),
-             P.Call(256, 1, 128, 2048, 2048), P.Call(128, 1, 256, 1500, 1500)] + _calls(1, 6000, kinds=("blocks", "tokens"))
-    beside = [P.cover_rule(c) for c in calls]
-    over = 0
-    for c, both in zip(calls, P.plans(exe, calls, beside)):
-        p, q = both
+             P.Call(256, 1, 128, 2048, 2048), P.Call(128, 1, 256, 1500, 1500)] + _calls(1, 6000)
+    over = other = 0
+    for c, got in zip(calls, P.plans(exe, calls)):
+        if got is None:
+            continue
+        p, q, _ = got
         over += not _small(q)
         if _small(q):
             assert _small(p), (c, p, q)
-        if _small(p) == _small(q):
-            assert p.us <= q.us / 0.93 + 1e-9, (c, p, q)
-    assert over > 100  # the limit is reached
+        if _small(p) == _small(q) and (p.row_groups, p.S) != (q.row_groups, q.S):
+            assert p.us < 0.97 * q.us, (c, p, q)
+            other += 1
+    assert over > 100 and other > 500  # the limit is reached, and other plans are taken
 
 
 def test_limit_forces_the_tile_by_price(exe):
@@ -46,7 +55,7 @@ def test_limit_forces_the_tile_by_price(exe):
               P.Call(128, 1, 256, 1500, 1500)):
         one, two = P.plans(exe, [c, c], [(1, 2), (2, 2)])
         assert not _small(one[0])
-        assert one[0].us == min(one[1].us, two[1].us)
+        assert one[0].us == min(one[2].us, two[2].us)
         assert one[0].row_groups == 2
 
 
@@ -62,7 +71,7 @@ def test_calls_that_fit_in_covering_splits_fit(exe):
     for c, b, both in zip(calls, beside, P.plans(exe, calls, beside)):
         if both is None:
             continue
-        p, q = both
+        p, q = both[0], both[2]
         n += c.per_row
         if _small(q):
             assert _small(p), (c, p, q)
@@ -88,3 +97,26 @@ def test_per_row_lists_hold_their_entries(exe):
         assert p.long_lists == (not c.fp8 and p.row_groups == 1 and entries > 512)
         long += p.long_lists
     assert long > 50
+
+
+# (call, row groups, splits, measured microseconds): large calls of every
+# selection kind, cache and tile on an MI355X, whose blocks are more bytes than
+# their rows in and out (3.2 KB a row, which the prices leave out).  A quarter is
+# the prices' error: 9 to 17 % rms by kind over all timed calls.
+TIMED = [
+    (P.Call(32, 1, 16, 256, 256), 1, 8, 110), (P.Call(64, 1, 128, 128, 2048, tokens=True), 2, 4, 61),
+    (P.Call(64, 1, 128, 128, 2048, tokens=True), 1, 2, 57), (P.Call(380, 1, 32, 24, 24), 1, 1, 146),
+    (P.Call(533, 1, 128, 38, 19, fp8=True), 1, 1, 316),
+    (P.Call(686, 1, 16, 28, 1779, tokens=True), 1, 1, 313), (P.Call(9, 1, 64, 1240, 620), 1, 28, 93),
+    (P.Call(5, 1, 64, 896, 896, fp8=True), 1, 52, 77), (P.Call(217, 1, 16, 28, 875, tokens=True, fp8=True), 1, 1, 41),
+    (P.Call(274, 1, 96, 30, 898, tokens=True, fp8=True), 1, 1, 149),
+    (P.Call(162, 1, 40, 56, 1790, tokens=True, fp8=True), 1, 3, 83),
+    (P.Call(409, 1, 40, 6, 346, tokens=True), 1, 1, 47), (P.Call(256, 1, 128, 2048, 2048), 2, 2, 8050),
+]
+
+
+def test_prices_are_what_calls_take(exe):
+    calls = [c for c, _, _, _ in TIMED]
+    for (c, rg, S, us), got in zip(TIMED, P.plans(exe, calls, [t[1:3] for t in TIMED])):
+        assert (c.K if c.tokens else c.K * 64) * (576 if c.fp8 else 1152) > 3200 * c.rows
+        assert abs(got[2].us / us - 1) <= 0.25, (c, rg, S, got[2].us, us)
