@@ -132,14 +132,14 @@ struct Planner {
     }
     q.long_lists = a.per_row && !a.fp8 && rg == 1 && q.sps * tile_qrows > kPerRowListShort;
     // What a call takes, microseconds.  A workgroup fills its CU, so that a
-    // grid goes in waves of one a CU; a work item takes a fixed part (its
-    // prologue, query rows and epilogue) and its blocks' time, and all together
-    // no less than their bytes take from memory (each tile of a job loads its
-    // blocks; the rows' own bytes are left out, with them the prices order plans
-    // worse); splits add the combine, by the bytes of the rows it reads.
-    // Fitted to 140000 timed plans of 28000 calls of 1..700 jobs of 8..256 rows x
-    // 1..1500 blocks or 16..6000 tokens (9 % rms in 128-row tiles, 9 to 17 % in
-    // 64-row ones).
+    // grid goes in waves of one a CU.  A wave takes as long as one of its work
+    // items, a fixed part (its prologue, query rows and epilogue) and its blocks'
+    // time, or as the bytes of all its blocks take from memory: a last wave of a
+    // few workgroups is bound by the former, a full one often by the latter.
+    // Splits add the combine, by the bytes of the rows it reads.  The rows' own
+    // bytes are left out.  Fitted to 140000 timed plans of 28000 calls of 1..700
+    // jobs of 8..256 rows x 1..1500 blocks or 16..6000 tokens (9 % rms in 128-row
+    // tiles, 9 to 17 % in 64-row ones).
     const double blocks = q.by_id ? (double)((most_blocks() + q.S - 1) / q.S)
                         : a.tokens ? (double)((q.sps + 63) / 64)
                         : a.per_row ? (double)std::min<int64_t>(std::max<int64_t>(a.NB, 1), q.sps * tile_qrows)
@@ -150,17 +150,18 @@ struct Planner {
     // by selection, cache and tile: half of a 64-row tile, one for all rows,
     // one of several, 128 rows
     static constexpr Rate kRate[2][2][4] = {
-        {{{6.1, 1.63, 5.5e6}, {8.3, 1.85, 5.1e6}, {8.7, 1.89, 6.8e6}, {14.4, 3.30, 4.2e6}},
+        {{{5.5, 1.62, 6.3e6}, {7.9, 1.83, 5.9e6}, {8.2, 1.85, 7.5e6}, {14.0, 3.27, 4.8e6}},
          {{6.6, 1.87, 5.5e6}, {9.4, 2.32, 5.5e6}, {9.4, 2.30, 5.5e6}, {14.1, 4.16, 5.5e6}}},
-        {{{5.2, 2.00, 5.4e6}, {8.0, 2.17, 4.7e6}, {8.6, 2.11, 6.4e6}, {14.2, 3.78, 5.2e6}},
+        {{{5.0, 1.99, 6.6e6}, {7.8, 2.19, 6.1e6}, {8.5, 2.17, 8.7e6}, {14.2, 3.78, 5.0e6}},
          {{5.7, 2.38, 5.5e6}, {8.4, 2.64, 5.5e6}, {9.2, 2.49, 5.5e6}, {14.5, 4.89, 5.5e6}}}};
     const Rate& rate = kRate[a.tokens][a.fp8][rg == 2 ? 3 : rows <= 32 ? 0 : rows <= 64 ? 1 : 2];
-    const double waves = std::ceil((double)a.R * q.row_tiles * q.S / a.cus);
-    q.us = waves * (rate.fixed + blocks * rate.block);
     // (rows with selections of their own share blocks, nobody here knows which)
-    if (!a.per_row)
-      q.us = std::max(q.us, rate.fixed + (double)a.R * q.row_tiles * Kb * kBlock * (kDLat + kDPe) *
-                                (a.fp8 ? 1 : 2) / rate.bytes);
+    const double item_bytes = a.per_row ? 0.0 : blocks * kBlock * (kDLat + kDPe) * (a.fp8 ? 1 : 2);
+    auto wave_us = [&](int64_t items) {
+      return rate.fixed + std::max(blocks * rate.block, (double)items * item_bytes / rate.bytes);
+    };
+    const int64_t items = a.R * q.row_tiles * q.S, rest = items % a.cus;
+    q.us = (double)(items / a.cus) * wave_us(a.cus) + (rest ? wave_us(rest) : 0.0);
     if (q.S > 1) q.us += 1.8 + 0.4e-6 * (double)ws_rows_bytes(q.S);
     return q;
   }
@@ -182,8 +183,8 @@ struct Planner {
     // of 2048 tokens 67 and 39.  Several waves of shorter splits where one wave
     // leaves CUs idle: 281 jobs of 8 rows x 86 fp8 blocks 327 us in one split,
     // 241 in three.  A plan has to promise 3 % over the covering one, about what
-    // the prices are off between plans of one call: over the timed calls one in
-    // 2000 then takes 2 % more than in the covering plan, and the mean is 8.7 %
+    // the prices are off between plans of one call: of the timed calls one in
+    // 4000 then takes 2 % more than in the covering plan, and the mean is 9.3 %
     // less (9.5 with the best plan of each call; a fourth wave adds nothing).
     // A plan whose split rows fit the allocation-free entry's scratch (64 MiB)
     // goes before one whose rows do not, for every entry; where a list's limit
