@@ -40,6 +40,7 @@ struct Planner {
   int row_groups = 0;      // of every plan, or 0: either
   const char* refused = nullptr;
   Plan cover{};            // the fewest splits that give every compute unit a workgroup
+  bool keep32 = false;     // split rows are held in fp32, whatever their number
 
   explicit Planner(const PlanArgs& args) : a(args), rows(a.Mq * a.H) {
     Kb = a.tokens ? (a.K + 63) / 64 : a.K;  // a token selection's slots fill K / 64 blocks
@@ -78,6 +79,10 @@ struct Planner {
     int64_t S = std::min<int64_t>((a.cus + units - 1) / units, std::max<int64_t>(most_blocks() / 2, 1));
     if (S == 2 && !by_id() && Kb <= 5) S = 1;
     cover = plan_of(groups, std::max<int64_t>(S, 1));
+    // Sums that the covering plan holds in fp32 (in registers from the first
+    // block to the last, or in a few split rows) are held so in any other.
+    keep32 = a.n_splits == 0 && (cover.S == 1 || !ws_half(cover.S));
+    cover = plan_of(groups, cover.S);  // priced with its own rows
   }
 
   int64_t row_tiles_of(int rg) const { return (rows + 64 * rg - 1) / (64 * rg); }
@@ -95,9 +100,12 @@ struct Planner {
   // Split rows in the workspace, then their scales (fp16 rows only), then their
   // lse values and maxima.  fp16 rows halve the workspace round trip, which pays
   // from about a megabyte of split rows on; tiny workspaces keep fp32 rows,
-  // whose epilogue is a little shorter.
+  // whose epilogue is a little shorter, and so do plans of more splits than the
+  // covering one where that holds fp32: 300 jobs of 16 rows x 64 blocks, one
+  // split to cover the chip, take 256 us in that, 242 in three with fp32 rows
+  // (240 with fp16 ones).
   uint64_t split_rows(int64_t S) const { return (uint64_t)a.R * S * rows; }
-  bool ws_half(int64_t S) const { return split_rows(S) * kDLat * 4 >= kWsHalfMinBytes; }
+  bool ws_half(int64_t S) const { return !keep32 && split_rows(S) * kDLat * 4 >= kWsHalfMinBytes; }
   uint64_t ws_rows_bytes(int64_t S) const { return split_rows(S) * kDLat * (ws_half(S) ? 2 : 4); }
   uint64_t ws_size(int64_t S) const { return ws_rows_bytes(S) + 3 * split_rows(S) * 4; }
   bool fits(const Plan& q) const { return q.S <= 1 || ws_size(q.S) <= kPlanScratch; }

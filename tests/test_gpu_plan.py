@@ -70,3 +70,25 @@ def test_automatic_plans(R, Mq, H, K, NB, tokens, per_row):
         e = (got - want).abs().amax(-1) / want.abs().amax(-1)
         assert float(e.max()) <= 2 ** -8 + 2 ** -11, float(e.max())
         assert float((lse[r, Mq - 1].double().cpu() - want_l).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("R,H,K,tokens", [(300, 16, 64, False), (269, 8, 96, False), (258, 16, 1000, True)])
+def test_sums_stay_in_fp32(R, H, K, tokens):
+    """More jobs than compute units, a few of them in a last wave: one split that
+    sums in registers covers the chip, and other plans keep its fp32.  With zero
+    queries every weight is 1, exact in bf16, and a row is the mean of its
+    tokens: fp32 sums of 4096 terms stay within 2^-16 of the row's largest value
+    (a row rounded to fp16 is off by up to 2^-12 of it)."""
+    print(f"case: fp32 sums R={R} H={H} K={K} tokens={tokens}", flush=True)
+    t = _inputs(R, 1, H, min(K, 96) if not tokens else K, 96 if not tokens else 30, tokens, False, 7300 + R)
+    out, lse = mla.sparse_partial_attn(torch.zeros_like(t["q_lat"]), torch.zeros_like(t["q_pe"]), t["ckv"], t["kpe"],
+                                       t["table"], t["sel"], SCALE, tokens=tokens)
+    torch.cuda.synchronize()
+    for r in (0, R // 2, R - 1):
+        ids = t["sel"][r].long()
+        rows = (t["ckv"][t["table"][r][ids // 64].long(), ids % 64] if tokens
+                else t["ckv"][t["table"][r][ids].long()].reshape(-1, 512))
+        want = rows.double().mean(0)
+        err = (out[r, 0].double() - want).abs().amax() / want.abs().amax()
+        assert float(err) <= 2 ** -16, float(err)
+        assert float((lse[r].double() - np.log(rows.shape[0])).abs().max()) <= 1e-5

@@ -99,6 +99,24 @@ def test_per_row_lists_hold_their_entries(exe):
     assert long > 50
 
 
+def test_sums_held_in_fp32_stay_in_fp32(exe):
+    """Where the covering plan sums in fp32 registers or keeps its split rows in
+    fp32, no other plan rounds them to fp16."""
+    calls = [P.Call(300, 1, 64, 64, 64), P.Call(295, 1, 32, 25, 25), P.Call(282, 1, 64, 50, 50),
+             P.Call(300, 1, 16, 64, 64)] + _calls(5, 8000)
+    more = 0
+    for c, got in zip(calls, P.plans(exe, calls)):
+        if got is None:
+            continue
+        p, q, _ = got
+        if q.S == 1 or c.R * q.S * c.rows * 2048 < 1 << 20:
+            assert not p.half and not q.half, (c, p, q)
+            more += p.S > q.S
+        else:
+            assert q.half
+    assert more > 20
+
+
 # (call, row groups, splits, measured microseconds): large calls of every
 # selection kind, cache and tile on an MI355X, whose blocks are more bytes than
 # their rows in and out (3.2 KB a row, which the prices leave out).  A quarter is
