@@ -158,12 +158,14 @@ typedef struct {
  * two kernels without another call's kernels between them.
  * Graph capture: a call captured on a stream uses that stream's workspace
  * as it was at capture time.  The workspace cannot grow while the stream is
- * being captured (MLA_ERR_UNSUPPORTED): make the same call, or a larger one,
- * on the stream before capturing.  Replay the graph on the stream it was
- * captured on, or keep other calls on that stream from running at the same
- * time as the replay (they share the buffer).  Under global-mode capture,
- * a call on another stream that has to grow its workspace allocates device
- * memory, which that capture mode forbids.
+ * being captured: the call then takes the fewest splits that cover the chip,
+ * which may need less or none (another rounding of the same result), or is
+ * refused (MLA_ERR_UNSUPPORTED).  Make the same call on the stream before
+ * capturing it (a larger call may take fewer splits).  Replay the graph on
+ * the stream it was captured on, or keep other calls on that stream from
+ * running at the same time as the replay (they share the buffer).  Under
+ * global-mode capture, a call on another stream that has to grow its
+ * workspace allocates device memory, which that capture mode forbids.
  */
 mla_status_t mla_sparse_partial_attn(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
                                      const mla_tensor_t* ckv_pool, const mla_tensor_t* kpe_pool,

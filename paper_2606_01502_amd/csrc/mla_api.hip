@@ -312,13 +312,36 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     const mla::Planner planner({R, Mq, H, NB, K, tokens, per_row, fp8, opts ? opts->n_splits : 0,
                                 opts ? opts->row_tile : 0, device_cus()});
     if (planner.refused) return fail(MLA_ERR_UNSUPPORTED, planner.refused);
-    const mla::Plan plan = planner.choose();
+    mla::Plan plan = planner.choose();
+    hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
+    std::unique_lock<std::mutex> ws_lock;  // held until the combine is queued
+    void* ws = nullptr;
+    if (plan.S > 1 && no_alloc) {
+      const uint64_t need = planner.ws_size(plan.S);
+      if (need > (uint64_t)MLA_NOALLOC_SCRATCH_BYTES)
+        return fail(MLA_ERR_UNSUPPORTED,
+                    "this call's split-K partials need " + std::to_string(need) +
+                        " bytes, more than the " + std::to_string((long long)MLA_NOALLOC_SCRATCH_BYTES) +
+                        "-byte scratch array of the allocation-free entry point (fewer jobs or "
+                        "splits per call)");
+      if ((st = scratch_address(&ws)) != MLA_OK) return st;
+    } else if (plan.S > 1) {
+      st = get_workspace(hs, planner.ws_size(plan.S), &ws, ws_lock);
+      // Where the workspace cannot grow (the stream is being captured, or memory
+      // is short) the covering plan may do with less, often with none.
+      if (st != MLA_OK && planner.a.n_splits == 0 && planner.cover.S < plan.S) {
+        if (ws_lock.owns_lock()) ws_lock.unlock();
+        plan = planner.cover;
+        st = plan.S > 1 ? get_workspace(hs, planner.ws_size(plan.S), &ws, ws_lock) : MLA_OK;
+        if (st == MLA_OK) g_last_error.clear();
+      }
+      if (st != MLA_OK) return st;
+    }
     const int row_groups = plan.row_groups;
     const int64_t row_tiles = plan.row_tiles, S = plan.S, sps = plan.sps;
     const bool by_id = plan.by_id;
     if (R * row_tiles * S > INT32_MAX) return fail(MLA_ERR_UNSUPPORTED, "grid too large");
 
-    hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
     mla::PartialParams p{};
     p.q_lat = (const uint16_t*)q_lat->data;
     p.q_pe = (const uint16_t*)q_pe->data;
@@ -344,10 +367,10 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     p.split_by_id = by_id ? 1 : 0;
     p.q_jobs = (int32_t)std::max<int64_t>(Rq, 1);
     p.q_rep = (int32_t)(Rq > 0 ? R / Rq : 1);
+    p.long_lists = plan.long_lists ? 1 : 0;
     // split-major numbering once a split's row tiles fill an XCD's share of
     // the grid (below that the combine's reads of a tile's splits on one XCD
     // are worth more than the shared block loads)
-    p.long_lists = plan.long_lists ? 1 : 0;
     p.tiles_fast = by_id && row_tiles >= 8 ? 1 : 0;
     p.row_tiles = (int32_t)row_tiles;
     p.by_splits = mla::make_div(S);
@@ -364,24 +387,10 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     p.out_s0 = out_lat->stride[0]; p.out_s1 = out_lat->stride[1]; p.out_s2 = out_lat->stride[2];
     p.lse = (float*)out_lse->data;
     p.lse_s0 = out_lse->stride[0]; p.lse_s1 = out_lse->stride[1]; p.lse_s2 = out_lse->stride[2];
-    std::unique_lock<std::mutex> ws_lock;  // held until the combine is queued
     if (S > 1) {
       const size_t n_part_rows = (size_t)R * S * rows;
       p.ws_f16 = planner.ws_half(S);
       const size_t o_bytes = planner.ws_rows_bytes(S);
-      const size_t ws_bytes = planner.ws_size(S);
-      void* ws = nullptr;
-      if (no_alloc) {
-        if (ws_bytes > (size_t)MLA_NOALLOC_SCRATCH_BYTES)
-          return fail(MLA_ERR_UNSUPPORTED,
-                      "this call's split-K partials need " + std::to_string(ws_bytes) +
-                          " bytes, more than the " + std::to_string((long long)MLA_NOALLOC_SCRATCH_BYTES) +
-                          "-byte scratch array of the allocation-free entry point (fewer jobs or "
-                          "splits per call)");
-        if ((st = scratch_address(&ws)) != MLA_OK) return st;
-      } else if ((st = get_workspace(hs, ws_bytes, &ws, ws_lock)) != MLA_OK) {
-        return st;
-      }
       p.ws_o32 = (float*)ws;
       p.ws_o16 = (uint16_t*)ws;
       p.ws_scale = (float*)((char*)ws + o_bytes);

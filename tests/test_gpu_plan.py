@@ -92,3 +92,49 @@ def test_sums_stay_in_fp32(R, H, K, tokens):
         err = (out[r, 0].double() - want).abs().amax() / want.abs().amax()
         assert float(err) <= 2 ** -16, float(err)
         assert float((lse[r].double() - np.log(rows.shape[0])).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("R,H,K,cover,tile", [(300, 16, 64, 1, 64), (136, 128, 64, 2, 128)])
+def test_captured_with_the_covering_plan_s_workspace(R, H, K, cover, tile):
+    """A call that covers the chip in fewer splits than its plan takes is
+    captured with no more workspace than those need (none for one split), and
+    gives their result; replays repeat it, with eager work between them."""
+    print(f"case: capture R={R} H={H} K={K}", flush=True)
+    t = _inputs(R, 1, H, K, K, False, False, 7400 + R)
+    args = (t["q_lat"], t["q_pe"], t["ckv"], t["kpe"], t["table"], t["sel"], SCALE)
+    ref = mla.sparse_partial_attn(*args, n_splits=cover, row_tile=tile)  # (on another stream)
+    out, lse = torch.empty_like(ref[0]), torch.empty_like(ref[1])
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        if cover > 1:
+            mla.sparse_partial_attn(*args, out, lse, n_splits=cover, row_tile=tile)
+            stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            mla.sparse_partial_attn(*args, out, lse)
+        for rep in range(3):
+            out.fill_(float("nan"))
+            lse.fill_(float("nan"))
+            stream.synchronize()
+            g.replay()
+            stream.synchronize()
+            assert torch.equal(out, ref[0]) and torch.equal(lse, ref[1]), rep
+            mla.sparse_partial_attn(*args)  # eager: the plan's own workspace
+            stream.synchronize()
+    torch.cuda.synchronize()
+
+
+def test_capture_without_the_covering_workspace_is_refused():
+    print("case: capture refused", flush=True)
+    t = _inputs(136, 1, 128, 64, 64, False, False, 7450)
+    out = torch.empty((136, 1, 128, 512), device=G.device())
+    lse = torch.empty((136, 1, 128), device=G.device())
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        g = torch.cuda.CUDAGraph()
+        with pytest.raises(mla.MlaError) as e:
+            with torch.cuda.graph(g, stream=stream):
+                mla.sparse_partial_attn(t["q_lat"], t["q_pe"], t["ckv"], t["kpe"], t["table"], t["sel"], SCALE, out, lse)
+        assert e.value.status == mla.MLA_ERR_UNSUPPORTED and "capture" in str(e.value)
+    torch.cuda.synchronize()
