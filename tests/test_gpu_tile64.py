@@ -167,3 +167,26 @@ def test_allocation_free_calls_with_long_lists(R, Mq, H, K, NB, n_q):
         s = (q_lat[r % n_q, i].double().cpu() @ k_lat.T + q_pe[r % n_q, i].double().cpu() @ k_pe.T) * 576 ** -0.5
         G.assert_parity(out[r, i].double().cpu().numpy(), lse[r, i].double().cpu().numpy(),
                         (torch.softmax(s, -1) @ k_lat).numpy(), torch.logsumexp(s, -1).numpy(), f"job {r} row {i}")
+
+
+@pytest.mark.parametrize("h", [8, 40])
+def test_normaliser_is_a_correctly_rounded_reciprocal(h):
+    # zero queries: every weight is 1, and job r's first token alone has a value
+    # (1 in every column), so that a row is 1 / (r + 1); r + 1 runs over the
+    # counts of a list
+    print(f"case: normaliser h={h}", flush=True)
+    R = 1024
+    dev = G.device()
+    ckv = torch.zeros((17, 64, 512), dtype=torch.bfloat16, device=dev)
+    ckv[16, 0] = 1.0
+    kpe = torch.zeros((17, 64, 64), dtype=torch.bfloat16, device=dev)
+    table = torch.arange(17, dtype=torch.int32, device=dev).expand(R, 17).contiguous()
+    sel = torch.arange(-1, R - 1, dtype=torch.int32, device=dev).expand(R, R).contiguous()
+    sel[:, 0] = 16 * 64
+    sel[torch.arange(R, device=dev)[None, :] > torch.arange(R, device=dev)[:, None]] = -1
+    q = torch.zeros((R, 1, h, 512), dtype=torch.bfloat16, device=dev)
+    out, lse = mla.sparse_partial_attn(q, q[..., :64].contiguous(), ckv, kpe, table, sel, 1.0, n_splits=1,
+                                       row_tile=64, tokens=True)
+    torch.cuda.synchronize()
+    want = (1.0 / np.arange(1, R + 1, dtype=np.float64)).astype(np.float32)
+    assert np.array_equal(out.cpu().numpy(), np.broadcast_to(want[:, None, None, None], (R, 1, h, 512)))
