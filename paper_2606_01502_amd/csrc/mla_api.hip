@@ -379,7 +379,6 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     p.by_jobs = mla::make_div(p.q_jobs);
     p.by_rep = mla::make_div(p.q_rep);
     p.by_K = mla::make_div(std::max<int64_t>(K, 1));
-    p.grid8 = (int32_t)(R * row_tiles * S % 8 ? 0 : R * row_tiles * S / 8);
     p.scale_log2 = (float)((double)scale * 1.4426950408889634074);
     p.out_wire = wire ? 1 : 0;
     p.out16 = (uint16_t*)out_lat->data;

@@ -67,9 +67,10 @@ struct PartialParams {
   // kPerRowListShort entries (bf16 caches only)
   int32_t long_lists;
   // divisors: n_splits, row_tiles, H, q_jobs, q_rep, and K (per-row selections);
-  // grid8: workgroups / 8 when 8 divides them, else 0
+  // first: work item of the launch's first workgroup; grid8: its workgroups / 8
+  // when 8 divides them, else 0 (both set by the launch)
   Div by_splits, by_tiles, by_H, by_jobs, by_rep, by_K;
-  int32_t grid8;
+  int32_t first, grid8;
   float scale_log2;  // softmax scale * log2(e)
   // destination: direct (n_splits == 1) or split-K workspace.  out_wire: the
   // bf16 wire form (Section 3.2): bf16 rows at out16 (element strides out_s*)

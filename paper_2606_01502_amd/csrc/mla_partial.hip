@@ -55,6 +55,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "mla_kernels.h"
@@ -793,7 +794,7 @@ void partial_kernel(const PartialParams p) {
   // of the same residue class, which then meet in the L2 of one or two XCDs
   // instead of all eight (the query rows, read once per split, are what is
   // fetched more than once instead, the smaller of the two).
-  const int w_id = p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8);
+  const int w_id = p.first + (p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8));
   const bool tiles_fast = PR && p.tiles_fast;
   int s_idx, rt, r_num;
   if (tiles_fast) {
@@ -1702,7 +1703,7 @@ void tile64_kernel(const PartialParams p) {
   const int n16 = lane & 15, g = lane >> 4;  // S^T: row (or token) and dim group
   const int n32 = lane & 31, g2 = lane >> 5;  // O^T: row (or column) and token group
 
-  const int w_id = p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8);
+  const int w_id = p.first + (p.grid8 == 0 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * p.grid8 + (int)(blockIdx.x / 8));
   const bool tiles_fast = PR && p.tiles_fast;
   int s_idx, rt, r_num;
   if (tiles_fast) {
@@ -2394,23 +2395,31 @@ void tile64_kernel(const PartialParams p) {
 
 }  // namespace
 
+// One launch holds less than 2^32 threads: work items go out 2^31 threads at a
+// time (4 M work items of the eight-wave kernel).
+template <class Kernel>
+static void launch_items(Kernel kernel, PartialParams p, int items, int threads, hipStream_t s) {
+  const int most = (int)((1ll << 31) / threads);
+  for (int first = 0; first < items;) {
+    const int n = std::min(most, items - first);
+    p.first = first;
+    p.grid8 = n % 8 ? 0 : n / 8;
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, s, p);
+    if (n == items - first) return;
+    first += n;
+  }
+}
+
 template <int KV, int SEL = kSelShared>
 static void launch_kv(const PartialParams& p, int grid, int row_groups, hipStream_t s) {
-  if (row_groups == 2) {
-    hipLaunchKernelGGL((partial_kernel<2, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
-    return;
-  }
-  if constexpr (KV == kKvBf16 && SEL == kSelPerRow) {
-    if (p.long_lists) {
-      hipLaunchKernelGGL((partial_kernel<1, KV, SEL>), dim3(grid), dim3(256), 0, s, p);
-      return;
-    }
-  }
+  if (row_groups == 2) return launch_items(partial_kernel<2, KV, SEL>, p, grid, 256, s);
+  if constexpr (KV == kKvBf16 && SEL == kSelPerRow)
+    if (p.long_lists) return launch_items(partial_kernel<1, KV, SEL>, p, grid, 256, s);
   // jobs of 32 rows at most: half a tile
   if (p.rows <= 32)
-    hipLaunchKernelGGL((tile64_kernel<KV, SEL, 1>), dim3(grid), dim3(512), 0, s, p);
+    launch_items(tile64_kernel<KV, SEL, 1>, p, grid, 512, s);
   else
-    hipLaunchKernelGGL((tile64_kernel<KV, SEL, 2>), dim3(grid), dim3(512), 0, s, p);
+    launch_items(tile64_kernel<KV, SEL, 2>, p, grid, 512, s);
 }
 
 hipError_t launch_partial(const PartialParams& p, int R, int kv, int row_groups, int sel_kind,

@@ -103,3 +103,28 @@ def test_fetch_with_pool_past_4gib():
     ref_c, ref_k = F.splice(chunk_c, chunk_k, small_c, small_k, table_small, 50, 0, 10000.0, 0)
     assert np.array_equal(got_c, ref_c) and np.array_equal(got_k, ref_k)
     assert float(ckv[0, :p_big - 6].float().abs().max()) == 0.0
+
+
+def test_more_jobs_than_one_launch_holds():
+    """2^23 + 5 one-row jobs: work items of 512 threads past the 2^32 threads of
+    one launch.  The jobs share one query row and repeat 64 pool blocks, so that
+    job r's row is that of job r % 64."""
+    print("case: 2^23 + 5 jobs", flush=True)
+    dev = G.device()
+    R, P = (1 << 23) + 5, 64
+    w = W.random_case(890, R=1, Mq=1, H=1, P=P, NB=1, K=1)
+    t = G.upload(w)
+    table = (torch.arange(R, dtype=torch.int32, device=dev) % P).view(R, 1)
+    sel = torch.zeros((R, 1), dtype=torch.int32, device=dev)
+    args = (t["q_lat"], t["q_pe"], t["ckv"], t["kpe"])
+    ref, ref_l = mla.sparse_partial_attn(*args, table[:P], sel[:P], w.scale, wire=True)
+    out, lse = mla.sparse_partial_attn(*args, table, sel, w.scale, wire=True)
+    torch.cuda.synchronize()
+    ref, ref_l = ref.view(P, 512), ref_l.view(P, 2)
+    out, lse = out.view(R, 512), lse.view(R, 2)
+    for lo in range(0, R, 1 << 20):
+        n = min(1 << 20, R - lo)
+        idx = torch.arange(lo, lo + n, device=dev) % P
+        assert torch.equal(out[lo:lo + n], ref[idx]) and torch.equal(lse[lo:lo + n], ref_l[idx]), lo
+    full, full_l = oracle.partial(w.q_lat, w.q_pe, w.ckv, w.kpe, np.array([[7]], np.int32), w.sel, w.scale)
+    assert G.row_errors(ref[7:8].double().cpu().numpy(), full.reshape(1, 512)).max() <= G.OUT_REL_TOL
