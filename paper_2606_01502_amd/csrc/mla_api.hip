@@ -376,7 +376,6 @@ mla_status_t partial_call(const mla_tensor_t* q_lat, const mla_tensor_t* q_pe,
     p.by_splits = mla::make_div(S);
     p.by_tiles = mla::make_div(row_tiles);
     p.by_H = mla::make_div(H);
-    p.by_jobs = mla::make_div(p.q_jobs);
     p.by_rep = mla::make_div(p.q_rep);
     p.by_K = mla::make_div(std::max<int64_t>(K, 1));
     p.scale_log2 = (float)((double)scale * 1.4426950408889634074);

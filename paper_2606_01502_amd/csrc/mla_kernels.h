@@ -23,12 +23,12 @@ constexpr uint64_t kWsHalfMinBytes = 1ull << 20;
 // floors agree.  (A division by a value the compiler does not know takes about
 // 30 dependent instructions; a 64-row work item started with five of them.)
 struct Div {
-  uint32_t d, m, s;
+  uint32_t m, s;
 };
 inline Div make_div(int64_t d) {
   uint32_t l = 0;
   while ((1ll << l) < d) ++l;
-  return Div{(uint32_t)d, (uint32_t)((1ull << (31 + l)) / (uint64_t)d + 1), 31 + l};
+  return Div{(uint32_t)((1ull << (31 + l)) / (uint64_t)d + 1), 31 + l};
 }
 __host__ __device__ inline int div_by(int n, const Div& d) {
   return (int)(((uint64_t)(uint32_t)n * d.m) >> d.s);
@@ -66,10 +66,10 @@ struct PartialParams {
   // 64-row tiles of per-row selections whose splits list more than
   // kPerRowListShort entries (bf16 caches only)
   int32_t long_lists;
-  // divisors: n_splits, row_tiles, H, q_jobs, q_rep, and K (per-row selections);
+  // divisors: n_splits, row_tiles, H, q_rep, and K (per-row selections);
   // first: work item of the launch's first workgroup; grid8: its workgroups / 8
   // when 8 divides them, else 0 (both set by the launch)
-  Div by_splits, by_tiles, by_H, by_jobs, by_rep, by_K;
+  Div by_splits, by_tiles, by_H, by_rep, by_K;
   int32_t first, grid8;
   float scale_log2;  // softmax scale * log2(e)
   // destination: direct (n_splits == 1) or split-K workspace.  out_wire: the

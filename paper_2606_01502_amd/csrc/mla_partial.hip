@@ -2395,8 +2395,9 @@ void tile64_kernel(const PartialParams p) {
 
 }  // namespace
 
-// One launch holds less than 2^32 threads: work items go out 2^31 threads at a
-// time (4 M work items of the eight-wave kernel).
+// One launch holds less than 2^32 threads (past that its size wraps, without an
+// error): work items go out 2^31 threads at a time (4 M work items of the
+// eight-wave kernel).
 template <class Kernel>
 static void launch_items(Kernel kernel, PartialParams p, int items, int threads, hipStream_t s) {
   const int most = (int)((1ll << 31) / threads);
