@@ -69,7 +69,10 @@ struct PartialParams {
   // divisors: n_splits, row_tiles, H, q_rep, and K (per-row selections);
   // first: work item of the launch's first workgroup; grid8: its workgroups / 8
   // when 8 divides them, else 0 (both set by the launch)
-  Div by_splits, by_tiles, by_H, by_rep, by_K;
+  // (aligned so that scalar loads take them whole: 30.9 us for 31.1 otherwise,
+  // 256 requesters x 16 heads x 32 blocks)
+  alignas(32) Div by_splits;
+  Div by_tiles, by_H, by_rep, by_K;
   int32_t first, grid8;
   float scale_log2;  // softmax scale * log2(e)
   // destination: direct (n_splits == 1) or split-K workspace.  out_wire: the

@@ -82,7 +82,6 @@ struct Planner {
     // Sums that the covering plan holds in fp32 (in registers from the first
     // block to the last, or in a few split rows) are held so in any other.
     keep32 = a.n_splits == 0 && (cover.S == 1 || !ws_half(cover.S));
-    cover = plan_of(groups, cover.S);  // priced with its own rows
   }
 
   int64_t row_tiles_of(int rg) const { return (rows + 64 * rg - 1) / (64 * rg); }
@@ -211,9 +210,11 @@ struct Planner {
       if (row_groups && rg != row_groups) continue;
       const int64_t units = std::max<int64_t>(a.R * row_tiles_of(rg), 1);
       const int64_t most = std::max<int64_t>(most_blocks() / 2, 1);
+      int64_t last = 0;
       for (int waves = 0; waves <= 3; ++waves) {
         const int64_t S = std::max<int64_t>(1, std::min<int64_t>(waves * a.cus / units, most));
-        if (S == 2 && !by_id() && Kb <= 5) continue;
+        if (S == last || (S == 2 && !by_id() && Kb <= 5)) continue;
+        last = S;
         const Plan q = plan_of(rg, S);
         if (fits(plan) && !fits(q)) continue;
         if ((fits(q) && !fits(plan)) || q.us < best) {
