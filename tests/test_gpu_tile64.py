@@ -190,3 +190,46 @@ def test_normaliser_is_a_correctly_rounded_reciprocal(h):
     torch.cuda.synchronize()
     want = (1.0 / np.arange(1, R + 1, dtype=np.float64)).astype(np.float32)
     assert np.array_equal(out.cpu().numpy(), np.broadcast_to(want[:, None, None, None], (R, 1, h, 512)))
+
+
+@pytest.mark.parametrize("kind", ["blocks", "tokens", "per_row"])
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp8split"])
+@pytest.mark.parametrize("h", [8, 24])
+def test_maxima_of_whole_blocks(h, kv, kind):
+    """A row's maximum is taken over the 64 tokens of its first block, so that the
+    heaviest of them weighs 1, exact in bf16.  Here that token is in the second
+    half and 256 / 1.5 times as heavy as the others: 1.5 / 256 is exact too,
+    170.67 (its weight against the first half's maximum) would round to 171 and
+    move the row by 5e-4.  fp32 scores and sums leave 2^-16."""
+    print(f"case: maxima of blocks h={h} {kv} {kind}", flush=True)
+    dev = G.device()
+    heavy = 41
+    lat = torch.zeros((3, 64, 512))
+    pe = torch.zeros((3, 64, 64))
+    lat[:2, heavy] = 1.0  # block 2: nobody's heavy token (scores 0)
+    pe[:2, heavy, 0] = 1.0
+    kw = {}
+    if kv == "bf16":
+        ckv, kpe = lat.bfloat16().to(dev), pe.bfloat16().to(dev)
+    else:
+        ckv, kpe = (t.to(torch.float8_e4m3fn).view(torch.uint8).to(dev) for t in (lat, pe))
+        one = torch.ones(3, device=dev)
+        kw = dict(ckv_scale=one, kpe_scale=one if kv == "fp8" else one.clone())
+    mq = 2 if kind == "per_row" else 1
+    q_lat = torch.zeros((1, mq, h, 512), dtype=torch.bfloat16, device=dev)
+    q_pe = torch.zeros((1, mq, h, 64), dtype=torch.bfloat16, device=dev)
+    q_pe[..., 0] = 1.0
+    table = torch.tensor([[2, 1, 0]], dtype=torch.int32, device=dev)
+    if kind == "tokens":
+        sel = torch.arange(64, 128, dtype=torch.int32, device=dev)[None]
+    elif kind == "blocks":
+        sel = torch.tensor([[1]], dtype=torch.int32, device=dev)
+    else:  # the second row's first block is the second of the tile's list
+        sel = torch.tensor([[[0, -1], [2, -1]]], dtype=torch.int32, device=dev)
+    out, lse = mla.sparse_partial_attn(q_lat, q_pe, ckv, kpe, table, sel, float(np.log(256 / 1.5)), n_splits=1,
+                                       row_tile=64, tokens=kind == "tokens", **kw)
+    torch.cuda.synchronize()
+    want = 1.0 / (1.0 + 63 * 1.5 / 256)
+    assert float((out[0, mq - 1].double() / want - 1).abs().max()) <= 2 ** -16
+    if kind == "per_row":
+        assert float(out[0, 0].abs().max()) == 0.0
