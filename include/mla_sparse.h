@@ -183,8 +183,8 @@ typedef struct {
    * other per-row selections split by logical block, split s taking blocks
    * s, s + n, s + 2n, ... (1..NB). */
   int32_t n_splits;
-  /* rows per work item: 64 or 128 (0 = automatic: 128 when Mq * H > 64 and
-   * the splits are long, else 64). */
+  /* rows per work item: 64 or 128 (0 = automatic: 64 when Mq * H <= 64; per-row
+   * selections 128 when the splits are long, else 64; any other the cheaper). */
   int32_t row_tile;
   /* output form: MLA_OUT_FP32 (0) or MLA_OUT_BF16_WIRE (see the partial
    * call's out_lat / out_lse). */
