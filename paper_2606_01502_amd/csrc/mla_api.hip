@@ -1,5 +1,5 @@
-// C ABI of libmla_sparse.so: argument validation, the split-K plan, the
-// split-K workspace and the kernel launches.  Declared in include/mla_sparse.h.
+// C ABI of libmla_sparse.so: argument validation, the split-K workspace and the
+// kernel launches (the plan is in mla_plan.h).  Declared in include/mla_sparse.h.
 
 #include <hip/hip_runtime.h>
 

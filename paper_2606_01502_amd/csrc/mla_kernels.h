@@ -178,7 +178,7 @@ constexpr int kAskBytes = 512;
 __host__ __device__ constexpr int ask_place(int stage) { return (stage & 1) * kAskBytes; }
 
 // Selection kinds: one block selection per job, one per query row, or one
-// token selection per job (bf16 caches only for the last two).
+// token selection per job.
 constexpr int kSelShared = 0;
 constexpr int kSelPerRow = 1;
 constexpr int kSelTokens = 2;
